@@ -122,7 +122,7 @@ def emit(obj, args):
 # grid and the batch-table builder): a stored HBM-traffic measurement of a
 # launch is reported only while its kernel's sources are unchanged.
 _COMMON_SOURCES = ["bitcos_kernel.h", "tables.h", "device_common.h", "batch.h", "batch.hip", "launch_common.h",
-                   "plan.h"]
+                   "plan.h", "start.h"]
 KERNEL_SOURCES = {
     "bitcos_fast_kernel": ["bitcos_fast.h", "gemv_bitcos.hip"] + _COMMON_SOURCES,
     "bitcos_diag_kernel": ["bitcos_diag.h", "bitcos_fast.h", "mfma_common.h", "gemv_bitcos.hip"] + _COMMON_SOURCES,

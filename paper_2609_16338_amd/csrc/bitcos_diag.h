@@ -189,7 +189,8 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
   constexpr int R = kWave / SEG;
   constexpr int S4 = SEG / 4;  // lanes of one row among the 16 lanes of a q group
   constexpr int NX = BF16 ? 16 : 8;
-  constexpr int WPB = diag_threads(W, BF16) / kWave;
+  constexpr int NT = diag_threads(W, BF16);
+  constexpr int WPB = NT / kWave;
   constexpr int D = diag_stages(W, BF16);
   // Sign buffer of one wave and stage: the largest step block (64 lanes x W
   // words, all non-zero) plus the dword a window reads past its start and
@@ -207,8 +208,6 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
   __shared__ uint4 sbuf1[WPB * SCR / 4];
   __shared__ uint4 sbuf2[D > 2 ? WPB * SCR / 4 : 1];
   static_assert(sizeof(tab) + 2 * sizeof(sbuf0) <= kLdsBytes, "diag kernel LDS");
-  build_fast_tables<BF16, CT>(tab, threadIdx.x, diag_threads(W, BF16));
-  __syncthreads();
 
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -218,7 +217,6 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
   const int per = (total + nwaves - 1) / nwaves;
   const int U0 = per * wave;
   const int U1 = min(U0 + per, total);
-  if (U0 >= U1) return;
   const FastLane fl = fast_lane<BF16, CT>(lane);
 
   // Lane layout: i = lane % 16 picks the row, the q group a quarter of its segments.
@@ -244,16 +242,15 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
   FastGen<R, TABLE> gen;
   gen.U = U0;
   gen.Uend = U1;
+  int fdi = 0;  // GEMV the workgroup's first wave starts on
   {
-    int lo = 0;
-    if constexpr (TABLE) {  // last descriptor with unit_begin <= U0
-      int hi = a.count;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (((CDesc*)a.table)[mid].unit_begin <= U0) lo = mid; else hi = mid;
-      }
+    if constexpr (TABLE) {  // of a wave without steps too: it helps to build the tables
+      const DescPair f = first_descs(a.table, a.count, min(U0, total - 1), min(per * static_cast<int>(blockIdx.x) * WPB, total - 1));
+      gen.enter(a, f.u);
+      fdi = f.v;
+    } else {
+      gen.enter(a, 0);
     }
-    gen.enter(a, lo);
   }
 
   FastStep st[D];
@@ -328,6 +325,36 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
   int nwl = W;
   rsrc_t ry = make_rsrc(nullptr, 0);
 
+  // GEMV d's scales, mode and output; the activations are loaded apart.
+  auto enter_x = [&](int d) {
+    xdi = d;
+    const auto& g = desc_at<TABLE>(a, d);
+    nwl = g.upr - w0;
+    ragged = g.upr != SEG * W;
+    mode = g.mode;
+    tensor_scale = half_bits_to_float(gp_u16(g.scales)[0]);
+    ry = make_rsrc(g.y, g.y_bytes);
+  };
+
+  // GEMV d's activations by the wave itself, 16 bytes a load (dword loads,
+  // which the compiler made of it without the table, took 15 us of a 27 us
+  // launch at 8 int8 words a lane); words past the row's end read zero.
+  auto load_x = [&](int d) {
+    const auto& g = desc_at<TABLE>(a, d);
+    const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
+    uint32_t xoff = static_cast<uint32_t>(w0) * NX * 4u;
+    asm volatile("" : "+v"(xoff));  // keeps the loads' offsets from being held (spilled) across the step loop
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+#pragma unroll
+      for (int d4 = 0; d4 < NX; d4 += 4) {
+        const u32x4_t v = ld128(rx, w < nwl ? xoff + 4u * (w * NX + d4) : kOOB);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xr[w][d4 + i] = v[i];
+      }
+    }
+  };
+
   // A step's output store is issued at the start of the next step, after
   // its wait (so that wait never waits on the store).
   bool pend = false;
@@ -356,21 +383,8 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
     // the next step's loads are issued, so that no wait inside the step
     // covers those loads.
     if (s.di != xdi) {
-      xdi = s.di;
-      const auto& g = desc_at<TABLE>(a, xdi);
-      nwl = g.upr - w0;
-      ragged = g.upr != SEG * W;
-      const int nx = max(0, min(W, nwl));
-      const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
-#pragma unroll
-      for (int w = 0; w < W; ++w) {
-        const uint32_t off = w < nx ? static_cast<uint32_t>(w0 + w) * NX * 4u : kOOB;
-#pragma unroll
-        for (int d = 0; d < NX; ++d) xr[w][d] = ld32(rx, off + 4u * d);
-      }
-      mode = g.mode;
-      tensor_scale = half_bits_to_float(gp_u16(g.scales)[0]);
-      ry = make_rsrc(g.y, g.y_bytes);
+      enter_x(s.di);
+      load_x(s.di);
       wait_vmem_all();
     }
     next();
@@ -469,6 +483,27 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
   [&]<int... Ks>(std::integer_sequence<int, Ks...>) {
     ((st[Ks] = gen.next(a), issue(std::integral_constant<int, Ks>{})), ...);
   }(std::make_integer_sequence<int, D - 1>{});
+
+  // The first step's loads are in flight while the workgroup builds the
+  // tables, and so are the activations of the GEMV its first wave starts on;
+  // a wave that starts on one with other activations loads its own
+  // when it decodes its first step.
+  FirstX<W * NX / 4, SEG, NT, WPB * SCR / 4> fx;
+  {
+    const auto& g = desc_at<TABLE>(a, fdi);
+    fx.fetch(make_rsrc(g.x, g.x_bytes), threadIdx.x);
+  }
+  build_fast_tables<BF16, CT, NT>(tab, threadIdx.x);
+  bool shared = true;
+  if (st[0].valid) {
+    enter_x(st[0].di);
+    if constexpr (TABLE) {
+      const auto &g = desc_at<TABLE>(a, st[0].di), &f = desc_at<TABLE>(a, fdi);
+      shared = g.x == f.x && g.x_bytes == f.x_bytes;
+    }
+  }
+  fx.share(reinterpret_cast<piece_t*>(sbuf1), threadIdx.x, j, shared, xr);
+  if (!shared) xdi = -1;
 
   bool more = true;
   while (more) {

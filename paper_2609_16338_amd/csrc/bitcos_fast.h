@@ -20,6 +20,8 @@
 #pragma once
 
 #include "bitcos_kernel.h"
+#include "mfma_common.h"
+#include "start.h"
 #include "tables.h"
 
 namespace bitcos_k {
@@ -110,7 +112,8 @@ template <int W, int SEG, bool BF16, bool TABLE>
 __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(const KernelArgs a) {
   constexpr int R = kWave / SEG;
   constexpr int NX = BF16 ? 16 : 8;
-  constexpr int WPB = fast_threads(W, BF16) / kWave;
+  constexpr int NT = fast_threads(W, BF16);
+  constexpr int WPB = NT / kWave;
   constexpr int D = FastCfg<W, BF16>::kStages;
   constexpr int NSC = FastCfg<W, BF16>::kSignChunks;
   constexpr int SCR = FastCfg<W, BF16>::kScratchDw;
@@ -127,8 +130,6 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   __shared__ uint4 sbuf0[WPB * SCR / 4];
   __shared__ uint4 sbuf1[WPB * SCR / 4];
   __shared__ uint4 sbuf2[D > 2 ? WPB * SCR / 4 : 1];
-  build_fast_tables<BF16, CT>(tab, threadIdx.x, fast_threads(W, BF16));
-  __syncthreads();
   const auto look = [&](uint32_t Pv, uint32_t Sv, const FastLane& f) { return fast_look<BF16, CT>(Pv, Sv, tab, f); };
   const auto math = [&](const Look<BF16>& Lk, const uint32_t* xv, Acc acc0) -> Acc {
     if constexpr (BF16)
@@ -145,7 +146,6 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   const int per = (total + nwaves - 1) / nwaves;
   const int U0 = per * wave;
   const int U1 = min(U0 + per, total);
-  if (U0 >= U1) return;
 
   const int rho = lane / SEG;
   const int j = lane % SEG;
@@ -165,16 +165,15 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   FastGen<R, TABLE> gen;
   gen.U = U0;
   gen.Uend = U1;
+  int fdi = 0;  // GEMV the workgroup's first wave starts on
   {
-    int lo = 0;
-    if constexpr (TABLE) {  // last descriptor with unit_begin <= U0
-      int hi = a.count;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (((CDesc*)a.table)[mid].unit_begin <= U0) lo = mid; else hi = mid;
-      }
+    if constexpr (TABLE) {  // of a wave without steps too: it helps to build the tables
+      const DescPair f = first_descs(a.table, a.count, min(U0, total - 1), min(per * static_cast<int>(blockIdx.x) * WPB, total - 1));
+      gen.enter(a, f.u);
+      fdi = f.v;
+    } else {
+      gen.enter(a, 0);
     }
-    gen.enter(a, lo);
   }
 
   // Ring of stages.
@@ -254,6 +253,41 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   rsrc_t ry = make_rsrc(nullptr, 0);
   const uint32_t voff_y = 4u * static_cast<uint32_t>(rho);
 
+  // GEMV d's scales, mode and output; the activations are loaded apart.
+  auto enter_x = [&](int d) {
+    xdi = d;
+    const auto& g = desc_at<TABLE>(a, d);
+    nwl = g.upr - w0;
+    ragged = g.upr != SEG * W;
+    mode = g.mode;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const int gi = min(g0 + q, max(g.ngroups - 1, 0));
+      xs[q] = (mode & kModeXscale) ? gp_f32(g.xscale)[gi] : 1.0f;
+    }
+    tensor_scale = half_bits_to_float(gp_u16(g.scales)[0]);
+    ry = make_rsrc(g.y, g.y_bytes);
+  };
+
+  // GEMV d's activations by the wave itself, 16 bytes a load (dword loads,
+  // which the compiler made of it without the table, took 15 us of a 27 us
+  // launch at 8 int8 words a lane); words past the row's end read zero.
+  auto load_x = [&](int d) {
+    const auto& g = desc_at<TABLE>(a, d);
+    const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
+    uint32_t xoff = static_cast<uint32_t>(w0) * NX * 4u;
+    asm volatile("" : "+v"(xoff));  // keeps the loads' offsets from being held (spilled) across the step loop
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+#pragma unroll
+      for (int d4 = 0; d4 < NX; d4 += 4) {
+        const u32x4_t v = ld128(rx, w < nwl ? xoff + 4u * (w * NX + d4) : kOOB);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xr[w][d4 + i] = v[i];
+      }
+    }
+  };
+
   // A step's output store is issued at the start of the next step, after
   // its wait (so that wait never waits on the store).
   bool pend = false;
@@ -282,26 +316,8 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     // for before the next step's loads are issued, so that no wait inside
     // the step covers those loads.
     if (s.di != xdi) {
-      xdi = s.di;
-      const auto& g = desc_at<TABLE>(a, xdi);
-      nwl = g.upr - w0;
-      ragged = g.upr != SEG * W;
-      const int nx = max(0, min(W, nwl));
-      const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
-#pragma unroll
-      for (int w = 0; w < W; ++w) {
-        const uint32_t off = w < nx ? static_cast<uint32_t>(w0 + w) * NX * 4u : kOOB;
-#pragma unroll
-        for (int d = 0; d < NX; ++d) xr[w][d] = ld32(rx, off + 4u * d);
-      }
-      mode = g.mode;
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        const int gi = min(g0 + q, max(g.ngroups - 1, 0));
-        xs[q] = (mode & kModeXscale) ? gp_f32(g.xscale)[gi] : 1.0f;
-      }
-      tensor_scale = half_bits_to_float(gp_u16(g.scales)[0]);
-      ry = make_rsrc(g.y, g.y_bytes);
+      enter_x(s.di);
+      load_x(s.di);
       wait_vmem_all();
     }
     next();
@@ -413,6 +429,27 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   [&]<int... Ks>(std::integer_sequence<int, Ks...>) {
     ((st[Ks] = gen.next(a), issue(std::integral_constant<int, Ks>{})), ...);
   }(std::make_integer_sequence<int, D - 1>{});
+
+  // The first step's loads are in flight while the workgroup builds the
+  // tables, and so are the activations of the GEMV its first wave starts on;
+  // a wave that starts on one with other activations loads its own
+  // when it decodes its first step.
+  FirstX<W * NX / 4, SEG, NT, WPB * SCR / 4> fx;
+  {
+    const auto& g = desc_at<TABLE>(a, fdi);
+    fx.fetch(make_rsrc(g.x, g.x_bytes), threadIdx.x);
+  }
+  build_fast_tables<BF16, CT, NT>(tab, threadIdx.x);
+  bool shared = true;
+  if (st[0].valid) {
+    enter_x(st[0].di);
+    if constexpr (TABLE) {
+      const auto &g = desc_at<TABLE>(a, st[0].di), &f = desc_at<TABLE>(a, fdi);
+      shared = g.x == f.x && g.x_bytes == f.x_bytes;
+    }
+  }
+  fx.share(reinterpret_cast<piece_t*>(sbuf1), threadIdx.x, j, shared, xr);
+  if (!shared) xdi = -1;
 
   bool more = true;
   while (more) {

@@ -117,7 +117,7 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
   __shared__ uint32_t sstage[WPB * kMfmaRows * kSignStride];
   __shared__ uint4 xbufs[WPB * mfma_xbuf_bytes(BF16) / 16];
   static_assert(sizeof(tab) + sizeof(sstage) + sizeof(xbufs) <= kLdsBytes, "small-batch kernel LDS");
-  build_fast_tables<BF16, CT>(tab, threadIdx.x, THREADS);
+  build_fast_tables<BF16, CT, THREADS>(tab, threadIdx.x);
   __syncthreads();
 
   const int lane = threadIdx.x & 63;

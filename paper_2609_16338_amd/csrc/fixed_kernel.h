@@ -28,6 +28,7 @@
 #include "device_common.h"
 #include "launch_common.h"
 #include "plan.h"
+#include "start.h"
 
 namespace fixed_k {
 
@@ -90,9 +91,10 @@ struct StepGen {
   }
 };
 
-// The wave's contiguous unit range of a persistent launch; returns false if empty.
+// The wave's contiguous unit range of a persistent launch (empty where
+// U >= Uend), and the GEMV the workgroup's first wave starts on.
 template <int R, bool TABLE, int WPB = kBlock / kWave>
-__device__ __forceinline__ bool wave_range(const KernelArgs& a, StepGen<R, TABLE>& gen) {
+__device__ __forceinline__ int wave_range(const KernelArgs& a, StepGen<R, TABLE>& gen) {
   const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + (threadIdx.x >> 6));
   const int64_t nwaves = static_cast<int64_t>(gridDim.x) * WPB;
   const int64_t per = (a.total_units + nwaves - 1) / nwaves;
@@ -100,14 +102,20 @@ __device__ __forceinline__ bool wave_range(const KernelArgs& a, StepGen<R, TABLE
   gen.Uend = min(gen.U + per, a.total_units);
   gen.di = 0;
   if constexpr (TABLE) {
-    int lo = 0, hi = a.count;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (((CDesc*)a.table)[mid].unit_begin <= gen.U) lo = mid; else hi = mid;
-    }
-    gen.di = __builtin_amdgcn_readfirstlane(lo);
+    const DescPair f = first_descs(a.table, a.count, min(gen.U, a.total_units - 1),
+                                   min(per * blockIdx.x * WPB, a.total_units - 1));
+    gen.di = f.u;
+    return f.v;
   }
-  return gen.U < gen.Uend;
+  return 0;
+}
+
+// Whether GEMVs d and f have the same activations.
+template <bool TABLE>
+__device__ __forceinline__ bool same_x(const KernelArgs& a, int d, int f) {
+  if constexpr (!TABLE) return true;
+  const auto &g = desc_at<TABLE>(a, d), &h = desc_at<TABLE>(a, f);
+  return g.x == h.x && g.x_bytes == h.x_bytes;
 }
 
 // Common epilogue: reduce the lane partials of one row and store.  SC holds
@@ -219,24 +227,50 @@ __device__ __forceinline__ void build_trit5_i8(Trit5TablesI8& tb, int v) {
   }
 }
 
-__device__ __forceinline__ void build_trit5_bf16(Trit5TablesBf16& tb, int tid, int nthreads) {
-  for (int idx = tid; idx < 256 * kTrit5Copies; idx += nthreads) {
+typedef unsigned u32v4 __attribute__((ext_vector_type(4)));
+
+// Every entry is computed once, into copy 0, and then moved to its other
+// copies with all of a thread's reads in flight together.
+template <int NT>
+__device__ __forceinline__ void build_trit5_bf16(Trit5TablesBf16& tb, int tid) {
+  constexpr int NC = kTrit5Copies;
+  static_assert(NT >= 256 && NT % NC == 0, "a thread keeps its column of the copy");
+  if (tid < 256) {
     int w[5];
-    trit5_digits(idx / kTrit5Copies, w);
+    trit5_digits(tid, w);
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       uint32_t h[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
       for (int t = 0; t < 5; ++t) h[p + t] = w[t] == 0 ? 0u : (w[t] > 0 ? 0x3F80u : 0xBF80u);
-      tb.t[p][idx] = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+      tb.t[p][tid * NC] = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
     }
   }
+  __syncthreads();
+  constexpr int kMoves = (256 * NC + NT - 1) / NT;
+  const int k = tid % NC;
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    u32v4* const base = reinterpret_cast<u32v4*>(tb.t[p]);
+    u32v4 v[kMoves];
+#pragma unroll
+    for (int i = 0; i < kMoves; ++i)
+      if ((i + 1) * NT <= 256 * NC || tid + i * NT < 256 * NC) v[i] = base[tid + i * NT - k];
+#pragma unroll
+    for (int i = 0; i < kMoves; ++i)
+      if ((i + 1) * NT <= 256 * NC || tid + i * NT < 256 * NC) base[tid + i * NT] = v[i];
+  }
+}
+
+// Four consecutive dwords through a buffer resource (dword aligned; dwords
+// past its range read zero).
+__device__ __forceinline__ u32v4 ld128(rsrc_t r, uint32_t off) {
+  return __builtin_bit_cast(u32v4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
 }
 
 // A table entry read as one 16-byte vector.  Its fourth dword is always zero
 // and unused; read through a uint4 the compiler drops it and splits the rest
 // into an 8-byte and a 4-byte read, twice the LDS instructions.
-typedef unsigned u32v4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ u32v4 lds_read16(const uint4* p) { return *reinterpret_cast<const u32v4*>(p); }
 
 // Byte i of the lane's aligned code stream A.
@@ -245,16 +279,16 @@ __device__ __forceinline__ uint32_t code_byte(const uint32_t (&A)[NA], int i) {
   return (A[i >> 2] >> (8 * (i & 3))) & 0xFFu;
 }
 
+// Pieces of 16 bytes that the workgroup's first activations pass through LDS at once.
+constexpr int kXRoom = 512;
+
 template <int BK, int SEG, bool BF16, bool TABLE>
 __global__ void __launch_bounds__(fixed_threads(false, BF16, BK)) trit5_gemv_kernel(const KernelArgs a) {
   using Tables = typename std::conditional<BF16, Trit5TablesBf16, Trit5TablesI8>::type;
-  constexpr int WPB = fixed_threads(false, BF16, BK) / kWave;
+  constexpr int NT = fixed_threads(false, BF16, BK);
+  constexpr int WPB = NT / kWave;
   __shared__ Tables tab;
-  if constexpr (BF16)
-    build_trit5_bf16(tab, threadIdx.x, fixed_threads(false, BF16, BK));
-  else
-    build_trit5_i8(tab, threadIdx.x);
-  __syncthreads();
+  __shared__ piece_t xbuf[kXRoom];
 
   constexpr int R = kWave / SEG;
   constexpr int NX = BF16 ? 64 : 32;             // activation dwords per block
@@ -262,7 +296,7 @@ __global__ void __launch_bounds__(fixed_threads(false, BF16, BK)) trit5_gemv_ker
   using Acc = typename std::conditional<BF16, float, int>::type;
 
   StepGen<R, TABLE> gen;
-  if (!wave_range<R, TABLE, WPB>(a, gen)) return;
+  const int fdi = wave_range<R, TABLE, WPB>(a, gen);
   const int lane = threadIdx.x & 63;
   const int rho = lane / SEG;
   const int j = lane % SEG;
@@ -291,10 +325,53 @@ __global__ void __launch_bounds__(fixed_threads(false, BF16, BK)) trit5_gemv_ker
   void* ydst = nullptr;
   uint32_t ybytes = 0;
 
+  // GEMV d's scales, mode and output; the activations are loaded apart.
+  auto enter_x = [&](int d) {
+    xdi = d;
+    const auto& g = desc_at<TABLE>(a, d);
+    load_xscales<BK>(g, b0, xs);
+    tensor_scale = half_bits_to_float(gp_u16(g.scales)[0]);
+    mode = g.mode;
+    ydst = g.y;
+    ybytes = g.y_bytes;
+  };
+  // GEMV d's activations by the wave itself.
+  auto load_x = [&](int d) {
+    const auto& g = desc_at<TABLE>(a, d);
+    const int nbl = g.upr - b0;
+    const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
+    uint32_t xoff = static_cast<uint32_t>(b0) * NX * 4u;
+    asm volatile("" : "+v"(xoff));  // keeps the loads' offsets from being held across the step loop
+#pragma unroll
+    for (int t = 0; t < BK; ++t) {
+#pragma unroll
+      for (int d4 = 0; d4 < NX; d4 += 4) {
+        const u32v4 v = ld128(rx, t < nbl ? xoff + 4u * (t * NX + d4) : kOOB);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xr[t][d4 + i] = v[i];
+      }
+    }
+  };
+
+  // The first step's loads and the activations of the GEMV the workgroup's
+  // first wave starts on are in flight while the tables are built; a wave
+  // that starts on one with other activations loads its own.
   Step s1 = gen.next(a);
   uint32_t cw1[ND], o1;
   uint16_t SC1[BK];
   load_c(s1, cw1, o1, SC1);
+  FirstX<BK * NX / 4, SEG, NT, kXRoom> fx;
+  {
+    const auto& f = desc_at<TABLE>(a, fdi);
+    fx.fetch(make_rsrc(f.x, f.x_bytes), threadIdx.x);
+  }
+  if constexpr (BF16)
+    build_trit5_bf16<NT>(tab, threadIdx.x);
+  else
+    build_trit5_i8(tab, threadIdx.x);
+  const bool shared = !s1.valid || same_x<TABLE>(a, s1.di, fdi);
+  if (s1.valid && shared) enter_x(s1.di);
+  fx.share(xbuf, threadIdx.x, j, shared, xr);
   while (s1.valid) {
     const Step s0 = s1;
     uint32_t A[ND - 1];
@@ -304,21 +381,8 @@ __global__ void __launch_bounds__(fixed_threads(false, BF16, BK)) trit5_gemv_ker
 #pragma unroll
     for (int t = 0; t < BK; ++t) SC0[t] = SC1[t];
     if (s0.di != xdi) {
-      xdi = s0.di;
-      const auto& g = desc_at<TABLE>(a, xdi);
-      const int nbl = max(0, min(BK, g.upr - b0));
-      const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
-#pragma unroll
-      for (int t = 0; t < BK; ++t) {
-        const uint32_t off = t < nbl ? static_cast<uint32_t>(b0 + t) * NX * 4u : kOOB;
-#pragma unroll
-        for (int d = 0; d < NX; ++d) xr[t][d] = ld32(rx, off + 4u * d);
-      }
-      load_xscales<BK>(g, b0, xs);
-      tensor_scale = half_bits_to_float(gp_u16(g.scales)[0]);
-      mode = g.mode;
-      ydst = g.y;
-      ybytes = g.y_bytes;
+      enter_x(s0.di);
+      load_x(s0.di);
       wait_vmem_all();
     }
     // The next step's loads, issued after the activations of a GEMV the wave
@@ -406,13 +470,12 @@ __device__ __forceinline__ void build_bit2_bf16(Bit2TablesBf16& tb, int tid, int
 
 template <int WB, int SEG, bool BF16, bool TABLE>
 __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kernel(const KernelArgs a) {
-  constexpr int WPB = fixed_threads(true, BF16, WB) / kWave;
-  __shared__ typename std::conditional<BF16, Bit2TablesBf16, char>::type tab;
-  if constexpr (BF16) {
-    build_bit2_bf16(tab, threadIdx.x, fixed_threads(true, BF16, WB));
-    __syncthreads();
-  }
-
+  constexpr int NT = fixed_threads(true, BF16, WB);
+  constexpr int WPB = NT / kWave;
+  struct alignas(16) XBuf {
+    piece_t v[kXRoom];
+  };
+  __shared__ alignas(16) typename std::conditional<BF16, Bit2TablesBf16, XBuf>::type tab;
   constexpr int R = kWave / SEG;
   constexpr int NX = BF16 ? 8 : 4;  // activation dwords per 16-weight word
   using Acc = typename std::conditional<BF16, float, int>::type;
@@ -420,7 +483,7 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
   constexpr int NQ = Ends::kNQ;
 
   StepGen<R, TABLE> gen;
-  if (!wave_range<R, TABLE, WPB>(a, gen)) return;
+  const int fdi = wave_range<R, TABLE, WPB>(a, gen);
   const int lane = threadIdx.x & 63;
   const int rho = lane / SEG;
   const int j = lane % SEG;
@@ -456,10 +519,75 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
   void* ydst = nullptr;
   uint32_t ybytes = 0;
 
+  // GEMV d's scales, mode and output; the activations are loaded apart.
+  auto enter_x = [&](int d) {
+    xdi = d;
+    const auto& g = desc_at<TABLE>(a, d);
+    load_xscales<NQ>(g, g0, xs);
+    tensor_scale = half_bits_to_float(gp_u16(g.scales)[0]);
+    mode = g.mode;
+    ydst = g.y;
+    ybytes = g.y_bytes;
+  };
+  // From activations in natural order: the int8 word sums, or the bf16 pairs.
+  auto arrange_x = [&] {
+#pragma unroll
+    for (int w = 0; w < WB; ++w) {
+      xsum[w] = 0;
+      if constexpr (!BF16) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xsum[w] = sdot4(xr[w][i], 0x01010101u, xsum[w]);
+      } else {
+        uint32_t v[NX];
+#pragma unroll
+        for (int i = 0; i < NX; ++i) v[i] = xr[w][i];
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+            xr[w][2 * b + h] = __builtin_amdgcn_perm(v[4 * h + 2 + b / 2], v[4 * h + b / 2], b & 1 ? 0x07060302u : 0x05040100u);
+      }
+    }
+  };
+  // GEMV d's activations by the wave itself.
+  auto load_x = [&](int d) {
+    const auto& g = desc_at<TABLE>(a, d);
+    const int nul = g.upr - u0;
+    const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
+    uint32_t xoff = static_cast<uint32_t>(u0) * NX * 4u;
+    asm volatile("" : "+v"(xoff));  // keeps the loads' offsets from being held across the step loop
+#pragma unroll
+    for (int w = 0; w < WB; ++w) {
+#pragma unroll
+      for (int d4 = 0; d4 < NX; d4 += 4) {
+        const u32v4 q = ld128(rx, w < nul ? xoff + 4u * (w * NX + d4) : kOOB);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) xr[w][d4 + i] = q[i];
+      }
+    }
+    arrange_x();
+  };
+
+  // As in the five-trit kernel; the bf16 variant's activations pass through
+  // the memory of its table, which is built after them (four workgroups of
+  // 40 KB would fill the LDS to the last byte).
   Step s1 = gen.next(a);
   uint32_t cw1[WB];
   uint16_t SC1[NQ];
   load_c(s1, cw1, SC1);
+  FirstX<WB * NX / 4, SEG, NT, kXRoom> fx;
+  {
+    const auto& f = desc_at<TABLE>(a, fdi);
+    fx.fetch(make_rsrc(f.x, f.x_bytes), threadIdx.x);
+  }
+  const bool shared = !s1.valid || same_x<TABLE>(a, s1.di, fdi);
+  if (s1.valid && shared) enter_x(s1.di);
+  fx.share(reinterpret_cast<piece_t*>(&tab), threadIdx.x, j, shared, xr);
+  arrange_x();
+  if constexpr (BF16) {
+    build_bit2_bf16(tab, threadIdx.x, NT);
+    __syncthreads();
+  }
   while (s1.valid) {
     const Step s0 = s1;
     uint32_t cw0[WB];
@@ -469,38 +597,8 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
 #pragma unroll
     for (int q = 0; q < NQ; ++q) SC0[q] = SC1[q];
     if (s0.di != xdi) {
-      xdi = s0.di;
-      const auto& g = desc_at<TABLE>(a, xdi);
-      const int nul = max(0, min(WB, g.upr - u0));
-#pragma unroll
-      for (int w = 0; w < WB; ++w) {
-        const bool ok = w < nul;
-        const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
-        if constexpr (!BF16) {
-          const uint32_t off = ok ? static_cast<uint32_t>(u0 + w) * 16u : kOOB;
-          int s = 0;
-#pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            xr[w][d] = ld32(rx, off + 4u * d);
-            s = sdot4(xr[w][d], 0x01010101u, s);
-          }
-          xsum[w] = s;
-        } else {
-          const uint32_t off = ok ? static_cast<uint32_t>(u0 + w) * 32u : kOOB;
-#pragma unroll
-          for (int b = 0; b < 4; ++b)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-              xr[w][2 * b + h] = uint32_t(ld16(rx, off + 2u * (8 * h + b))) |
-                                 uint32_t(ld16(rx, off + 2u * (8 * h + 4 + b))) << 16;
-          xsum[w] = 0;
-        }
-      }
-      load_xscales<NQ>(g, g0, xs);
-      tensor_scale = half_bits_to_float(gp_u16(g.scales)[0]);
-      mode = g.mode;
-      ydst = g.y;
-      ybytes = g.y_bytes;
+      enter_x(s0.di);
+      load_x(s0.di);
       wait_vmem_all();
     }
     // The next step's loads, issued after the activations of a GEMV the wave

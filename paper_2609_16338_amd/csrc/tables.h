@@ -42,8 +42,12 @@ struct FastTables {
   alignas(256) uint8_t bytes[kT + 256u * kTStride];
 };
 
-template <bool BF16, int CT>
-__device__ __forceinline__ void build_fast_tables(FastTables<BF16, CT>& t, int tid, int nthreads) {
+// A 16-byte piece of a table as a plain vector (arrays of it stay in registers).
+typedef unsigned chunk16 __attribute__((ext_vector_type(4)));
+
+// NT: threads of the workgroup (all of them call).
+template <bool BF16, int CT, int NT>
+__device__ __forceinline__ void build_fast_tables(FastTables<BF16, CT>& t, int tid) {
   using Tb = FastTables<BF16, CT>;
   // Each of the 256 entries is computed once, into the first 16 bytes of its
   // row (E: copy 0, or copies 0 and 1 of the 8-byte int8 entries; T: copies 0
@@ -74,15 +78,31 @@ __device__ __forceinline__ void build_fast_tables(FastTables<BF16, CT>& t, int t
     q[(Tb::kT + e * Tb::kTStride) / 16] = make_uint4(glo, ghi, glo, ghi);
   }
   __syncthreads();
-  for (int idx = tid; idx < 256 * 16; idx += nthreads) {
-    const int k = idx & 15;
-    if (k) q[idx] = q[idx - k];
-  }
+  // Three of a thread's moves at once, so that their reads are in flight
+  // together (a rolled loop paid one LDS round trip per move); more of them
+  // spill beside the activations that are on their way.
   constexpr int TC = CT / 2;  // 16-byte chunks per T row
-  for (int idx = tid; idx < 256 * TC; idx += nthreads) {
-    const int k = idx % TC;
-    if (k) q[Tb::kT / 16 + idx] = q[Tb::kT / 16 + idx - k];
-  }
+  static_assert(NT % 16 == 0, "a thread keeps its column of the copy");
+  const auto copy = [&](auto row_chunks, uint4* rows) {
+    constexpr int RC = decltype(row_chunks)::value;
+    constexpr int kMoves = (256 * RC + NT - 1) / NT;
+    const int k = tid % RC;
+    chunk16* const base = reinterpret_cast<chunk16*>(rows);
+    constexpr int kAtOnce = 3;
+#pragma unroll
+    for (int i0 = 0; i0 < kMoves; i0 += kAtOnce) {
+      chunk16 v[kAtOnce];
+#pragma unroll
+      for (int i = i0; i < i0 + kAtOnce && i < kMoves; ++i)
+        if ((i + 1) * NT <= 256 * RC || tid + i * NT < 256 * RC) v[i - i0] = base[tid + i * NT - k];
+#pragma unroll
+      for (int i = i0; i < i0 + kAtOnce && i < kMoves; ++i)
+        if ((i + 1) * NT <= 256 * RC || tid + i * NT < 256 * RC) base[tid + i * NT] = v[i - i0];
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  copy(std::integral_constant<int, 16>{}, q);
+  copy(std::integral_constant<int, TC>{}, q + Tb::kT / 16);
 }
 
 // int8 arithmetic of one word from deposit-form lookups: perm(T[s], E[m])
