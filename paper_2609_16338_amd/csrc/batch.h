@@ -65,7 +65,8 @@ struct BatchHeader {
   int32_t any_grouped;   // some GEMV has group scales
   int32_t row_offsets;   // every BITCOS GEMV stores one sign offset per row
   int32_t small_batch;   // m == 1 rows longer than any batch-1 tile: the small-batch kernel
-  int32_t reserved[16];
+  int32_t split;         // small-batch kernel: waves that share a unit's K (1: a wave walks whole units)
+  int32_t reserved[15];
 };
 static_assert(sizeof(BatchHeader) == 128, "BatchHeader is 128 bytes");
 
@@ -111,11 +112,33 @@ inline int gemv_rows(GemvEntry gemv, const bitcos_layout* L, const void* blob_de
 // small-batch kernel with one activation row, when it takes the layout.
 bool batch1_on_small_batch(const bitcos_layout* L, int32_t x_dtype);
 
-// Count a descriptor in the small-batch kernel's steps: units of 32 rows,
-// each K / 512 steps (four 128-weight groups per step).  The kernel splits a
-// launch's steps evenly over its waves.
-inline void to_mfma_units(GemvDesc* d) {
-  d->units = static_cast<int64_t>((d->n + kMfmaUnitRows - 1) / kMfmaUnitRows) * ((d->ngroups + 3) / 4);
+// Units (of 32 rows) and steps of a unit (four 128-weight groups each) of a
+// descriptor in the small-batch kernel.
+inline int64_t mfma_units(const GemvDesc& d) { return (d.n + kMfmaUnitRows - 1) / kMfmaUnitRows; }
+inline int32_t mfma_steps(const GemvDesc& d) { return (d.ngroups + 3) / 4; }
+
+// Waves that share one unit's K: 1, 2, 4 or 8.  A wave that walks whole units
+// leaves most of the GPU idle when a launch has few of them (a 4096-row GEMV:
+// 128 units for 2048 waves, each 8 steps at K = 4096), so a unit is split
+// as far as all its parts still run at once and have a step.  Splitting
+// further costs more than it gives: the parts then run in turns, and each
+// counts its signs first and adds its sums to the others' through LDS.
+// Kernel times whole -> split (us, bf16): 4096 x 4096 with 4 rows 23.0 -> 9.2,
+// 4096 x 12288 with 4 rows 59.7 -> 17.3 (8 parts), 5120 x 25600 with one row
+// 120 -> 31 (8 parts), 25600 x 5120 with 16 rows 33 -> 27 (2 parts).
+constexpr int kMfmaWaves = 2048;  // 256 CUs x 8 waves
+inline int32_t mfma_split(int64_t units, int32_t most_steps) {
+  int32_t s = 1;
+  while (s < 8 && units * (2 * s) <= kMfmaWaves && 2 * s <= most_steps) s *= 2;
+  return s;
+}
+
+// Count a descriptor in the small-batch kernel's work: whole units when the
+// launch splits them; steps otherwise, which the kernel divides evenly over
+// its waves (GEMVs of different K in one launch leave no wave with several
+// times the others' work).
+inline void to_mfma_units(GemvDesc* d, int32_t split) {
+  d->units = mfma_units(*d) * (split > 1 ? 1 : mfma_steps(*d));
 }
 
 // Tile (per-lane units, lanes per row) the given layout runs with.

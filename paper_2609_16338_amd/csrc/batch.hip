@@ -131,6 +131,7 @@ static int build_small_batch(int32_t count, int32_t m, const bitcos_layout* layo
                              const float* const* xscale_dev, void* const* y_dev, BatchHeader* h,
                              GemvDesc* descs) {
   int64_t units = 0;
+  int32_t most_steps = 1;
   for (int32_t i = 0; i < count; ++i) {
     const bitcos_layout* L = &layouts[i];
     if (L->format != BITCOS_FMT_BITCOS) return L->format == BITCOS_FMT_TRIT5 || L->format == BITCOS_FMT_BIT2
@@ -141,7 +142,13 @@ static int build_small_batch(int32_t count, int32_t m, const bitcos_layout* layo
     if (st) return st;
     if (!mfma_layout_ok(L)) return BITCOS_E_UNSUPPORTED;
     if (xs) h->any_xscale = 1;
-    to_mfma_units(&descs[i]);
+    units += mfma_units(descs[i]);
+    most_steps = mfma_steps(descs[i]) > most_steps ? mfma_steps(descs[i]) : most_steps;
+  }
+  h->split = mfma_split(units, most_steps);
+  units = 0;
+  for (int32_t i = 0; i < count; ++i) {
+    to_mfma_units(&descs[i], h->split);
     descs[i].unit_begin = units;
     units += descs[i].units;
   }

@@ -60,7 +60,7 @@ struct KernelArgs {
   const GemvDesc* __restrict__ table;  // batch: descriptor table in device memory
   int64_t total_units;
   int32_t count;                       // descriptors in the table
-  int32_t pad;
+  int32_t split;                       // small-batch kernel: waves that share a unit
   GemvDesc one;                        // single GEMV: its descriptor
 };
 

@@ -12,6 +12,11 @@
 // each wave takes the units that start inside its equal share of the steps,
 // so GEMVs of different K in one launch leave no wave with several times the
 // others' work.
+// A launch of few units (batch.h: mfma_split) gives each unit to 2, 4 or 8
+// waves of a workgroup instead, which split its steps: every wave counts the
+// non-zeros of its part (one pass over the presence words, while the tables
+// are built) so that those after it know where their signs start, and the
+// parts' sums are added in order through LDS.
 //   * Lane l works on row n = l % 16 of each tile and, in every group, on its
 //     32-weight word g = l / 16, so the four lane groups of a row cover one
 //     group together and an MFMA never mixes two scale groups.
@@ -52,6 +57,7 @@
 #pragma once
 
 #include "mfma_common.h"
+#include "start.h"
 #include "tables.h"
 
 namespace bitcos_k {
@@ -103,7 +109,7 @@ struct MStep {
   bool valid;
 };
 
-template <bool BF16, bool XS, bool TABLE>
+template <bool BF16, bool XS, bool TABLE, bool SPLIT>
 __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(const KernelArgs a) {
   constexpr int CT = mfma_sign_copies(BF16);
   constexpr int THREADS = mfma_threads(BF16, XS);
@@ -116,20 +122,23 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
   __shared__ FastTables<BF16, CT> tab;
   __shared__ uint32_t sstage[WPB * kMfmaRows * kSignStride];
   __shared__ uint4 xbufs[WPB * mfma_xbuf_bytes(BF16) / 16];
-  static_assert(sizeof(tab) + sizeof(sstage) + sizeof(xbufs) <= kLdsBytes, "small-batch kernel LDS");
-  build_fast_tables<BF16, CT, THREADS>(tab, threadIdx.x);
-  __syncthreads();
+  __shared__ uint32_t part_nnz[SPLIT ? WPB * kMfmaRows : 1];  // split units: non-zeros of each row in each wave's part
+  static_assert(sizeof(tab) + sizeof(sstage) + sizeof(xbufs) + sizeof(part_nnz) <= kLdsBytes, "small-batch kernel LDS");
 
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + wv);
-  // The wave's share of the launch's steps: [S0, S1).
+  // Whole units: the wave's share [S0, U1) of the launch's steps.  Split
+  // units: `split` waves of a workgroup share unit `wave / split`.
+  const int split = SPLIT ? a.split : 1;
+  constexpr bool whole = !SPLIT;
   const int total = static_cast<int>(a.total_units);
   const int nwaves = static_cast<int>(gridDim.x) * WPB;
-  const int per = (total + nwaves - 1) / nwaves;
-  const int S0 = per * wave;
+  const int per = whole ? (total + nwaves - 1) / nwaves : 1;
+  const int part = whole ? 0 : wave & (split - 1);
+  const int S0 = whole ? per * wave : wave / split;
   const int U1 = min(S0 + per, total);
-  if (S0 >= U1) return;
+  bool has = S0 < U1;
 
   const int nr = lane & 15;
   const int g = lane >> 4;
@@ -183,26 +192,24 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
     load_offsets(same ? fdi : min(fdi + 1, a.count - 1), same ? (u + 1) * kMfmaRows : 0, start < U1, o);
   };
 
-  // First unit: the first one of the launch to start at or after S0.
+  // First unit: the first one of the launch to start at or after S0; and the
+  // steps [c0, c1) of it that are the wave's (of every unit, when whole).
   int u0 = 0;
-  {
-    int lo = 0;
-    if constexpr (TABLE) {  // last descriptor with unit_begin <= S0
-      int hi = a.count;
-      while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (((CDesc*)a.table)[mid].unit_begin <= S0) lo = mid; else hi = mid;
-      }
-    }
-    fetch_enter(lo);
+  fetch_enter(TABLE ? first_descs(a.table, a.count, min(S0, total - 1), 0).u : 0);
+  if (has && whole) {
     u0 = (S0 - fbeg + fC - 1) / fC;
     if (fbeg + u0 * fC >= fend) {  // no unit of this GEMV starts in the share
-      if (fend >= U1) return;
-      fetch_enter(fdi + 1);
+      has = fend < U1;
+      if (has) fetch_enter(fdi + 1);
       u0 = 0;
     }
-    if (fbeg + u0 * fC >= U1) return;
+    has = has && fbeg + u0 * fC < U1;
+  } else if (has) {
+    u0 = S0 - fbeg;
   }
+  const int c0 = whole ? 0 : fC * part / split;
+  const int c1 = whole ? 0 : fC * (part + 1) / split;
+  if (SPLIT) has = has && c0 < c1;
 
   // Step data: presence words, fp16 group scales and sign dwords of the
   // lane's row in each tile, and the row's sign position at the step start.
@@ -282,7 +289,10 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
   };
   auto advance = [&](const MStep& s) {
     MStep n = s;
-    if (s.c + 1 < fC) {
+    if constexpr (SPLIT) {
+      n.c = s.c + 1;
+      n.valid = n.c < c1;
+    } else if (s.c + 1 < fC) {
       n.c = s.c + 1;
     } else {  // the next unit: u + 1, or the next GEMV's first; it is the wave's if it starts before U1
       const int start = fbeg + (s.unit + 1) * fC;
@@ -304,6 +314,25 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
   float tscale = 0.0f;
   rsrc_t ry = make_rsrc(nullptr, 0);
 
+  auto decode_enter = [&](int d) {
+    ddi = d;
+    const auto& D = desc_at<TABLE>(a, ddi);
+    dn = D.n;
+    grouped = (D.mode & kModeGrouped) != 0;
+    raw = !BF16 && (D.mode & kModeRaw);
+    dadd = (D.mode & kModeAdd) != 0;
+    dxs = XS && (D.mode & kModeXscale);
+    scaled = !raw && (grouped || dxs);
+    tscale = half_bits_to_float(gp_u16(D.scales)[0]);
+    ry = make_rsrc(D.y, D.y_bytes);
+  };
+  // An output element from its sum (fp32, or int32 bits where !scaled int8).
+  auto finish = [&](float f, int i32) {
+    if (raw) return static_cast<uint32_t>(i32);
+    if (!scaled) f = BF16 ? tscale * (2.0f * f) : tscale * static_cast<float>(i32);
+    return __builtin_bit_cast(uint32_t, f);
+  };
+
   // Accumulators: batch rows 4 g + i of output row nr of each tile.
   float acc[RT][4];
   int iacc[RT][4];
@@ -315,18 +344,64 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
       iacc[r][i] = 0;
     }
 
-  // ---- prologue
+  // ---- prologue: the first step's loads are in flight while the workgroup
+  // builds the tables; the sign dwords need the wave's first sign position,
+  // in a split unit the row's offset and the non-zeros of the parts before.
   MStep fs;
   fs.di = fdi;
   fs.unit = u0;
-  fs.c = 0;
+  fs.c = c0;
   fs.last = fC == 1;
-  fs.valid = true;
+  fs.valid = has;
   Slot cur, nxt;
   uint32_t offn[RT];
-  load_offsets(fdi, u0 * kMfmaRows, true, cur.pos);
+  load_offsets(fdi, u0 * kMfmaRows, has, cur.pos);
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) offn[r] = 0;
+  }
+  uint32_t nnz[RT] = {0, 0};
+  if (SPLIT && has) {
+    // The lane's group of each of the part's steps, four steps' loads at a time.
+    constexpr int kAtOnce = 4;
+    const uint32_t lp = (static_cast<uint32_t>(nr) * static_cast<uint32_t>(fupr) + 4u * g) * 4u;
+    for (int c = c0; c < c1; c += kAtOnce) {
+      u32x4_t v[kAtOnce][RT];
+#pragma unroll
+      for (int t = 0; t < kAtOnce; ++t)
+#pragma unroll
+        for (int r = 0; r < RT; ++r) {
+          const bool in = c + t < c1 && 4 * (c + t) + g < fG;
+          const uint32_t sp = (static_cast<uint32_t>(u0 * kMfmaRows + kMfmaTile * r) * static_cast<uint32_t>(fupr) +
+                               16u * static_cast<uint32_t>(c + t)) * 4u;
+          v[t][r] = ld128_s(rb, in ? lp : kOOB, __builtin_amdgcn_readfirstlane(c + t < c1 ? sp : 0u));
+        }
+#pragma unroll
+      for (int t = 0; t < kAtOnce; ++t)
+#pragma unroll
+        for (int r = 0; r < RT; ++r)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) nnz[r] += __builtin_popcount(v[t][r][q]);
+    }
+#pragma unroll
+    for (int r = 0; r < RT; ++r) {  // over the row's four lanes
+      nnz[r] += xor16(nnz[r]);
+      nnz[r] += xor32(nnz[r]);
+    }
+  }
+  build_fast_tables<BF16, CT, THREADS>(tab, threadIdx.x);
+  if (SPLIT && g == 0) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) part_nnz[wv * kMfmaRows + kMfmaTile * r + nr] = nnz[r];
+  }
+  __syncthreads();
+  if (whole && !has) return;
+  for (int p = 0; SPLIT && p < part; ++p) {
+#pragma unroll
+    for (int r = 0; r < RT; ++r) cur.pos[r] += part_nnz[(wv - part + p) * kMfmaRows + kMfmaTile * r + nr];
+  }
   issue(fs, cur);
-  next_unit_offsets(u0, offn);
+  if constexpr (!SPLIT) next_unit_offsets(u0, offn);
 #pragma unroll
   for (int q = 0; q < 4; ++q) issue_x(fs, q);
 
@@ -375,18 +450,7 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
   for (;;) {
     const MStep cs = fs;
     if (!cs.valid) break;
-    if (cs.di != ddi) {
-      ddi = cs.di;
-      const auto& D = desc_at<TABLE>(a, ddi);
-      dn = D.n;
-      grouped = (D.mode & kModeGrouped) != 0;
-      raw = !BF16 && (D.mode & kModeRaw);
-      dadd = (D.mode & kModeAdd) != 0;
-      dxs = XS && (D.mode & kModeXscale);
-      scaled = !raw && (grouped || dxs);
-      tscale = half_bits_to_float(gp_u16(D.scales)[0]);
-      ry = make_rsrc(D.y, D.y_bytes);
-    }
+    if (cs.di != ddi) decode_enter(cs.di);
 
     // Fetch step t+1.  offn holds the offsets of the unit after step t's:
     // step t+1's own when it starts a unit.
@@ -396,7 +460,9 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
     // The unit after step t+1's is read only when step t+1 ends its unit (a
     // lane-masked branch: loads under a uniform branch into this
     // loop-carried register would make the compiler copy it into place).
-    if (lane_mask(fs.last)) next_unit_offsets(fs.unit, offn);
+    if constexpr (!SPLIT) {
+      if (lane_mask(fs.last)) next_unit_offsets(fs.unit, offn);
+    }
     issue(fs, nxt);
 
     // The groups at raised wave priority (as in the batch-1 kernels): int8
@@ -508,7 +574,7 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_wave_barrier();
 
-    if (cs.last) {  // store the unit: y[m][row]; rows past n and batch rows past M are dropped
+    if (whole && cs.last) {  // store the unit: y[m][row]; rows past n and batch rows past M are dropped
       const int row0 = cs.unit * kMfmaRows;
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
@@ -516,15 +582,7 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const uint32_t off = row < dn ? (static_cast<uint32_t>((4 * g + i) * dn) + row) * 4u : kOOB;
-          float f;
-          if (scaled)
-            f = acc[r][i];
-          else if constexpr (BF16)
-            f = tscale * (2.0f * acc[r][i]);
-          else
-            f = tscale * static_cast<float>(iacc[r][i]);
-          const uint32_t bits = raw ? static_cast<uint32_t>(iacc[r][i]) : __builtin_bit_cast(uint32_t, f);
-          put_y(bits, ry, off, 0, dadd, raw);
+          put_y(finish(acc[r][i], iacc[r][i]), ry, off, 0, dadd, raw);
           acc[r][i] = 0.0f;
           iacc[r][i] = 0;
         }
@@ -535,18 +593,52 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
     stage_signs(nxt);
     cur = nxt;
   }
+  if constexpr (whole) return;
+
+  // Split units: every part's sums go to its wave's transpose buffer (8 of
+  // 64 lanes' values, 2 KB), and each of the unit's waves adds 8 / split of
+  // them over the parts, in order, and stores.
+  static_assert(mfma_xbuf_bytes(BF16) >= RT * 4 * kWave * 4, "a wave's sums fit its transpose buffer");
+  uint32_t* const sums = reinterpret_cast<uint32_t*>(xbufs);
+  constexpr int kSumStride = mfma_xbuf_bytes(BF16) / 4;
+  if (S0 < U1) decode_enter(fdi);
+  const bool ints = !BF16 && !scaled;
+#pragma unroll
+  for (int r = 0; r < RT; ++r)
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      sums[wv * kSumStride + (4 * r + i) * kWave + lane] =
+          ints ? static_cast<uint32_t>(iacc[r][i]) : __builtin_bit_cast(uint32_t, acc[r][i]);
+  __syncthreads();
+  if (S0 >= U1) return;
+  for (int v = part; v < RT * 4; v += split) {
+    const uint32_t* p = sums + (wv - part) * kSumStride + v * kWave + lane;
+    float f = 0.0f;
+    int n = 0;
+    for (int k = 0; k < split; ++k) {
+      const uint32_t w = p[k * kSumStride];
+      if (ints)
+        n += static_cast<int>(w);
+      else
+        f += __builtin_bit_cast(float, w);
+    }
+    const int row = u0 * kMfmaRows + kMfmaTile * (v >> 2) + nr;
+    const uint32_t off = row < dn ? (static_cast<uint32_t>((4 * g + (v & 3)) * dn) + row) * 4u : kOOB;
+    put_y(finish(f, n), ry, off, 0, dadd, raw);
+  }
 }
 
 using MfmaFn = void (*)(const KernelArgs);
 
 template <bool BF16, bool XS>
-MfmaFn pick_mfma_t(bool table) {
-  return table ? bitcos_mfma_kernel<BF16, XS, true> : bitcos_mfma_kernel<BF16, XS, false>;
+MfmaFn pick_mfma_t(bool table, bool split) {
+  if (split) return table ? bitcos_mfma_kernel<BF16, XS, true, true> : bitcos_mfma_kernel<BF16, XS, false, true>;
+  return table ? bitcos_mfma_kernel<BF16, XS, true, false> : bitcos_mfma_kernel<BF16, XS, false, false>;
 }
 
-inline MfmaFn pick_mfma(bool bf16, bool xs, bool table) {
-  if (bf16) return xs ? pick_mfma_t<true, true>(table) : pick_mfma_t<true, false>(table);
-  return xs ? pick_mfma_t<false, true>(table) : pick_mfma_t<false, false>(table);
+inline MfmaFn pick_mfma(bool bf16, bool xs, bool table, bool split) {
+  if (bf16) return xs ? pick_mfma_t<true, true>(table, split) : pick_mfma_t<true, false>(table, split);
+  return xs ? pick_mfma_t<false, true>(table, split) : pick_mfma_t<false, false>(table, split);
 }
 
 }  // namespace bitcos_k

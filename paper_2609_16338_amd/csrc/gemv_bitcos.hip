@@ -83,7 +83,7 @@ int launch_bitcos(const BatchHeader& h, const GemvDesc* table_dev, const GemvDes
   a.table = table_dev;
   a.total_units = h.total_units;
   a.count = h.count;
-  a.pad = 0;
+  a.split = 1;
   a.one = one;
   const int threads = diag        ? bitcos_k::diag_threads(h.per_lane, bf16)
                       : streaming ? bitcos_k::fast_threads(h.per_lane, bf16)
@@ -109,8 +109,9 @@ extern "C" int bitcos_gemv(const bitcos_layout* L, const void* blob_dev, int32_t
     bitcos::GemvDesc d;
     int st = bitcos::make_desc(L, blob_dev, x_dev, xscale_dev, y_dev, x_dtype, y_mode, &d, m);
     if (st) return st;
-    bitcos::to_mfma_units(&d);
     bitcos::BatchHeader h{};
+    h.split = bitcos::mfma_split(bitcos::mfma_units(d), bitcos::mfma_steps(d));
+    bitcos::to_mfma_units(&d, h.split);
     h.magic = bitcos::kBatchMagic;
     h.version = BITCOS_LAYOUT_VERSION;
     h.format = BITCOS_FMT_BITCOS;
