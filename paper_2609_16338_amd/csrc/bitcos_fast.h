@@ -140,12 +140,8 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
 
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + wv);
   const int total = static_cast<int>(a.total_units);
-  const int nwaves = static_cast<int>(gridDim.x) * WPB;
-  const int per = (total + nwaves - 1) / nwaves;
-  const int U0 = per * wave;
-  const int U1 = min(U0 + per, total);
+  const auto range = unit_range<WPB>(total, wv);
 
   const int rho = lane / SEG;
   const int j = lane % SEG;
@@ -163,12 +159,12 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   const uint32_t wave_bits = static_cast<uint32_t>(wv) * SCR * 32u;
 
   FastGen<R, TABLE> gen;
-  gen.U = U0;
-  gen.Uend = U1;
+  gen.U = range.begin;
+  gen.Uend = range.end;
   int fdi = 0;  // GEMV the workgroup's first wave starts on
   {
     if constexpr (TABLE) {  // of a wave without steps too: it helps to build the tables
-      const DescPair f = first_descs(a.table, a.count, min(U0, total - 1), min(per * static_cast<int>(blockIdx.x) * WPB, total - 1));
+      const DescPair f = first_descs(a.table, a.count, min(range.begin, total - 1), min(range.first, total - 1));
       gen.enter(a, f.u);
       fdi = f.v;
     } else {
@@ -219,6 +215,13 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     const uint32_t soff_p = __builtin_amdgcn_readfirstlane(s.valid ? unit * row_bytes : kOOB);
 #pragma unroll
     for (int w = 0; w < W; ++w) P[k][w] = __builtin_amdgcn_raw_buffer_load_b32(rb, voff_p + 4u * w, soff_p, 0);
+    const uint32_t soff_q = __builtin_amdgcn_readfirstlane((s.valid && grouped) ? unit * row_scale_bytes : kOOB);
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) SC[k][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, voff_q[q], soff_q, 0);
+  };
+  auto issue_signs = [&](auto stage_c) {
+    constexpr int k = decltype(stage_c)::value;
+    const FastStep& s = st[k];
     // The step's sign block: dwords [off0 / 32, off1 / 32 + 1] are the most
     // any window reads.  Only the 16-byte pieces of that range are fetched,
     // straight into this wave's part of the stage buffer (lane l of chunk c
@@ -237,9 +240,6 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
                                                    voff_s, soff_s, 0, 0);
       }
     }
-    const uint32_t soff_q = __builtin_amdgcn_readfirstlane((s.valid && grouped) ? unit * row_scale_bytes : kOOB);
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) SC[k][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, voff_q[q], soff_q, 0);
   };
 
   // Decode side: lane state of the GEMV whose steps are being decoded.
@@ -425,21 +425,20 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     pend_ry = ry;
   };
 
-  // Prologue: steps 0 .. D-2 in flight.
-  [&]<int... Ks>(std::integer_sequence<int, Ks...>) {
-    ((st[Ks] = gen.next(a), issue(std::integral_constant<int, Ks>{})), ...);
-  }(std::make_integer_sequence<int, D - 1>{});
-
-  // The first step's loads are in flight while the workgroup builds the
-  // tables, and so are the activations of the GEMV its first wave starts on;
-  // a wave that starts on one with other activations loads its own
-  // when it decodes its first step.
+  // The first step's words and the activations of the GEMV the workgroup's
+  // first wave starts on are in flight while the tables are built, and so are
+  // the step's sign offsets; a wave that starts on a GEMV with other
+  // activations loads its own when it decodes its first step.
+  static_assert(D == 2, "one step in flight before the loop");
+  st[0] = gen.next(a);
   FirstX<W * NX / 4, SEG, NT, WPB * SCR / 4> fx;
   {
     const auto& g = desc_at<TABLE>(a, fdi);
     fx.fetch(make_rsrc(g.x, g.x_bytes), threadIdx.x);
   }
+  issue(std::integral_constant<int, 0>{});
   build_fast_tables<BF16, CT, NT>(tab, threadIdx.x);
+  issue_signs(std::integral_constant<int, 0>{});
   bool shared = true;
   if (st[0].valid) {
     enter_x(st[0].di);
@@ -448,7 +447,7 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
       shared = g.x == f.x && g.x_bytes == f.x_bytes;
     }
   }
-  fx.share(reinterpret_cast<piece_t*>(sbuf1), threadIdx.x, j, shared, xr);
+  fx.share(reinterpret_cast<piece_t*>(sbuf1), threadIdx.x, j, shared && st[0].valid, xr);
   if (!shared) xdi = -1;
 
   bool more = true;
@@ -465,6 +464,7 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
          decode(std::integral_constant<int, Ks>{}, [&] {
            st[nk] = gen.next(a);
            issue(std::integral_constant<int, nk>{});
+           issue_signs(std::integral_constant<int, nk>{});
          });
        }()),
        ...);

@@ -95,15 +95,13 @@ struct StepGen {
 // U >= Uend), and the GEMV the workgroup's first wave starts on.
 template <int R, bool TABLE, int WPB = kBlock / kWave>
 __device__ __forceinline__ int wave_range(const KernelArgs& a, StepGen<R, TABLE>& gen) {
-  const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + (threadIdx.x >> 6));
-  const int64_t nwaves = static_cast<int64_t>(gridDim.x) * WPB;
-  const int64_t per = (a.total_units + nwaves - 1) / nwaves;
-  gen.U = per * wave;
-  gen.Uend = min(gen.U + per, a.total_units);
+  const auto range = unit_range<WPB>(a.total_units, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+  gen.U = range.begin;
+  gen.Uend = range.end;
   gen.di = 0;
   if constexpr (TABLE) {
     const DescPair f = first_descs(a.table, a.count, min(gen.U, a.total_units - 1),
-                                   min(per * blockIdx.x * WPB, a.total_units - 1));
+                                   min(range.first, a.total_units - 1));
     gen.di = f.u;
     return f.v;
   }
@@ -371,7 +369,7 @@ __global__ void __launch_bounds__(fixed_threads(false, BF16, BK)) trit5_gemv_ker
     build_trit5_i8(tab, threadIdx.x);
   const bool shared = !s1.valid || same_x<TABLE>(a, s1.di, fdi);
   if (s1.valid && shared) enter_x(s1.di);
-  fx.share(xbuf, threadIdx.x, j, shared, xr);
+  fx.share(xbuf, threadIdx.x, j, shared && s1.valid, xr);
   while (s1.valid) {
     const Step s0 = s1;
     uint32_t A[ND - 1];
@@ -582,7 +580,7 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
   }
   const bool shared = !s1.valid || same_x<TABLE>(a, s1.di, fdi);
   if (s1.valid && shared) enter_x(s1.di);
-  fx.share(reinterpret_cast<piece_t*>(&tab), threadIdx.x, j, shared, xr);
+  fx.share(reinterpret_cast<piece_t*>(&tab), threadIdx.x, j, shared && s1.valid, xr);
   arrange_x();
   if constexpr (BF16) {
     build_bit2_bf16(tab, threadIdx.x, NT);

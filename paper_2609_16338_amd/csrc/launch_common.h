@@ -34,15 +34,18 @@ inline int bitcos_blocks_per_cu(const void* fn, int threads) {
 }
 
 // Blocks of `threads` threads for a persistent launch over `units` work units:
-// as many as the GPU keeps resident at once, and no more than one wave per
-// unit.  -1 on a HIP error.
+// as many as the GPU keeps resident at once, no more than a wave per unit
+// needs, but at least a block on every CU while there are units for them
+// (the kernels spread a launch's units over all of its blocks).  -1 on a HIP
+// error.
 inline int64_t persistent_blocks(const void* fn, int64_t units, int threads = 256) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return -1;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return -1;
   const int64_t resident = static_cast<int64_t>(cus) * bitcos_blocks_per_cu(fn, threads);
   const int64_t wpb = threads / 64;
-  const int64_t need = (units + wpb - 1) / wpb;
+  int64_t need = (units + wpb - 1) / wpb;
+  if (need < cus) need = units < cus ? units : cus;
   int64_t b = need < resident ? need : resident;
   return b < 1 ? 1 : b;
 }

@@ -46,6 +46,31 @@ __device__ __forceinline__ DescPair first_descs(const bitcos::GemvDesc* table, i
   return {find(U), find(V)};
 }
 
+// A wave's share [begin, end) of a launch's units: consecutive workgroups take
+// consecutive shares, as equal as whole units allow, and so do the waves of
+// each.  A launch of few units so keeps a wave or two busy on every CU rather
+// than a few full ones, whose waves wait for each other's issue slots (4096 x
+// 4096 int8 with the faster table build: 7.5 -> 6.3 us), and a large launch has
+// no wave with more than one unit above the others' (Qwen3-8B-like int8 set of
+// 8 layers 91.1 -> 86.8 us).
+template <class I>
+struct UnitRange {
+  I first;       // the workgroup's first unit
+  I begin, end;  // the wave's
+};
+template <int WAVES, class I>
+__device__ __forceinline__ UnitRange<I> unit_range(I total, int wv) {
+  const I b = static_cast<I>(blockIdx.x), g = static_cast<I>(gridDim.x);
+  const I q = total / g, r = total % g;  // the first r workgroups take one unit more
+  const I first = b * q + (b < r ? b : r);
+  const I n = q + (b < r ? 1 : 0);
+  // n wv / WAVES without a product of n, which may take all of I's bits.
+  const I nq = n / WAVES;
+  const int nr = static_cast<int>(n % WAVES);
+  const auto cut = [&](int w) { return first + nq * w + nr * w / WAVES; };
+  return {first, cut(wv), cut(wv + 1)};
+}
+
 // Activations of the GEMV that a workgroup starts on, fetched once for all of
 // its waves.  A lane keeps the activations of its consecutive units, so a
 // wave that reads them itself touches another cache line with every lane of

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 #include "bitcos_kernel.h"
 
@@ -42,67 +43,83 @@ struct FastTables {
   alignas(256) uint8_t bytes[kT + 256u * kTStride];
 };
 
-// A 16-byte piece of a table as a plain vector (arrays of it stay in registers).
+// A 16-byte piece of a table.
 typedef unsigned chunk16 __attribute__((ext_vector_type(4)));
 
-// NT: threads of the workgroup (all of them call).
+// The value of lane LANE of every 16-lane row, into the lanes of the row that
+// BANKS (one bit per four lanes) names.
+template <int LANE, int BANKS>
+__device__ __forceinline__ void row_bcast(chunk16& to, const chunk16& from) {
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    to[i] = static_cast<unsigned>(__builtin_amdgcn_update_dpp(static_cast<int>(to[i]), static_cast<int>(from[i]),
+                                                              0x150 + LANE, 0xF, BANKS, false));
+}
+
+// All threads of the workgroup (NT) call; the tables are complete after its
+// next barrier.  Every wave computes the 64 entries of one quarter of the
+// keys, one per lane, and writes its share of their copies: 1 KB a store,
+// whole rows of copies, each row's entry handed to its lanes by DPP.  The
+// 128 KB of stores take about 1000 cycles at the LDS's rate; moving the
+// copies from a first one in LDS took twice that and a barrier, on every
+// launch (with the rest of a launch's start, 256 x 1024 int8: 6.0 -> 5.3 us).
 template <bool BF16, int CT, int NT>
 __device__ __forceinline__ void build_fast_tables(FastTables<BF16, CT>& t, int tid) {
   using Tb = FastTables<BF16, CT>;
-  // Each of the 256 entries is computed once, into the first 16 bytes of its
-  // row (E: copy 0, or copies 0 and 1 of the 8-byte int8 entries; T: copies 0
-  // and 1); the other copies are then 16-byte moves from there, so building
-  // the tables costs every launch little next to its GEMVs.
-  uint4* q = reinterpret_cast<uint4*>(t.bytes);
-  if (tid < 256) {
-    const uint32_t e = static_cast<uint32_t>(tid);
-    uint32_t rk[8], g[8];
-    uint32_t r = 0;
+  static_assert(NT % 256 == 0, "waves share the quarters evenly");
+  constexpr int kShares = NT / 256;
+  chunk16* const q = reinterpret_cast<chunk16*>(t.bytes);
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int share = wv >> 2;
+  const int key0 = (wv & 3) * 64 + (lane & 48);  // first key of the lane's 16-lane row
+  const uint32_t e = static_cast<uint32_t>((wv & 3) * 64 + lane);
+  uint32_t rk[8], g[8];
+  uint32_t r = 0;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const uint32_t on = e >> b & 1;
-      rk[b] = on ? r : 0x0Cu;
-      r += on;
-      g[b] = on ? (BF16 ? 0xBFu : 0xFFu) : (BF16 ? 0x3Fu : 0x01u);
-    }
-    uint4 ev;
-    if constexpr (BF16) {
-      ev = make_uint4(bytes4(0x0C, rk[0], 0x0C, rk[1]), bytes4(0x0C, rk[2], 0x0C, rk[3]),
-                      bytes4(0x0C, rk[4], 0x0C, rk[5]), bytes4(0x0C, rk[6], 0x0C, rk[7]));
-    } else {
-      const uint32_t lo = bytes4(rk[0], rk[1], rk[2], rk[3]), hi = bytes4(rk[4], rk[5], rk[6], rk[7]);
-      ev = make_uint4(lo, hi, lo, hi);
-    }
-    const uint32_t glo = bytes4(g[0], g[1], g[2], g[3]), ghi = bytes4(g[4], g[5], g[6], g[7]);
-    q[e * 16] = ev;
-    q[(Tb::kT + e * Tb::kTStride) / 16] = make_uint4(glo, ghi, glo, ghi);
+  for (int b = 0; b < 8; ++b) {
+    const uint32_t on = e >> b & 1;
+    rk[b] = on ? r : 0x0Cu;
+    r += on;
+    g[b] = on ? (BF16 ? 0xBFu : 0xFFu) : (BF16 ? 0x3Fu : 0x01u);
   }
-  __syncthreads();
-  // Three of a thread's moves at once, so that their reads are in flight
-  // together (a rolled loop paid one LDS round trip per move); more of them
-  // spill beside the activations that are on their way.
-  constexpr int TC = CT / 2;  // 16-byte chunks per T row
-  static_assert(NT % 16 == 0, "a thread keeps its column of the copy");
-  const auto copy = [&](auto row_chunks, uint4* rows) {
-    constexpr int RC = decltype(row_chunks)::value;
-    constexpr int kMoves = (256 * RC + NT - 1) / NT;
-    const int k = tid % RC;
-    chunk16* const base = reinterpret_cast<chunk16*>(rows);
-    constexpr int kAtOnce = 3;
-#pragma unroll
-    for (int i0 = 0; i0 < kMoves; i0 += kAtOnce) {
-      chunk16 v[kAtOnce];
-#pragma unroll
-      for (int i = i0; i < i0 + kAtOnce && i < kMoves; ++i)
-        if ((i + 1) * NT <= 256 * RC || tid + i * NT < 256 * RC) v[i - i0] = base[tid + i * NT - k];
-#pragma unroll
-      for (int i = i0; i < i0 + kAtOnce && i < kMoves; ++i)
-        if ((i + 1) * NT <= 256 * RC || tid + i * NT < 256 * RC) base[tid + i * NT] = v[i - i0];
-      __builtin_amdgcn_sched_barrier(0);
+  chunk16 ev;
+  if constexpr (BF16) {
+    ev = {bytes4(0x0C, rk[0], 0x0C, rk[1]), bytes4(0x0C, rk[2], 0x0C, rk[3]), bytes4(0x0C, rk[4], 0x0C, rk[5]),
+          bytes4(0x0C, rk[6], 0x0C, rk[7])};
+  } else {
+    const uint32_t lo = bytes4(rk[0], rk[1], rk[2], rk[3]), hi = bytes4(rk[4], rk[5], rk[6], rk[7]);
+    ev = {lo, hi, lo, hi};
+  }
+  const uint32_t glo = bytes4(g[0], g[1], g[2], g[3]), ghi = bytes4(g[4], g[5], g[6], g[7]);
+  const chunk16 tv = {glo, ghi, glo, ghi};
+  [&]<int... Ws>(std::integer_sequence<int, Ws...>) {  // E: 16 chunks a row, key key0 + w
+    (([&] {
+       if (Ws % kShares != share) return;
+       chunk16 v = ev;
+       row_bcast<Ws, 0xF>(v, ev);
+       q[(key0 + Ws) * 16 + (lane & 15)] = v;
+     }()),
+     ...);
+  }(std::make_integer_sequence<int, 16>{});
+  constexpr int TC = CT / 2;       // chunks per T row
+  constexpr int kRows = 16 / TC;   // T rows per 16 lanes
+  constexpr int kBanks = (1 << (TC / 4)) - 1;  // the DPP banks of one T row
+  const auto t_rows = [&](auto w) {  // T: keys key0 + kRows w ..
+    constexpr int k = decltype(w)::value * kRows;
+    if (decltype(w)::value % kShares != share) return;
+    chunk16 v = tv;
+    row_bcast<k, kBanks>(v, tv);
+    if constexpr (kRows >= 2) row_bcast<k + 1, kBanks << (TC / 4)>(v, tv);
+    if constexpr (kRows == 4) {
+      row_bcast<k + 2, kBanks << (2 * (TC / 4))>(v, tv);
+      row_bcast<k + 3, kBanks << (3 * (TC / 4))>(v, tv);
     }
+    q[Tb::kT / 16 + (key0 + k) * TC + (lane & 15)] = v;
   };
-  copy(std::integral_constant<int, 16>{}, q);
-  copy(std::integral_constant<int, TC>{}, q + Tb::kT / 16);
+  [&]<int... Ws>(std::integer_sequence<int, Ws...>) {
+    (t_rows(std::integral_constant<int, Ws>{}), ...);
+  }(std::make_integer_sequence<int, TC>{});
 }
 
 // int8 arithmetic of one word from deposit-form lookups: perm(T[s], E[m])
