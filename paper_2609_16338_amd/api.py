@@ -18,6 +18,18 @@ from ._native import (FMT_BIT2, FMT_BITCOS, FMT_TRIT5, LaunchInfo, Layout, X_BF1
                       Y_F32, Y_F32_ADD, Y_I32_RAW, Y_I32_RAW_ADD)
 
 
+_torch = None
+
+
+def _t():
+    """torch, imported by the first call that takes device tensors."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _ptr(a: np.ndarray) -> ctypes.c_void_p:
     return ctypes.c_void_p(a.ctypes.data)
 
@@ -183,10 +195,16 @@ _GEMV = {FMT_BITCOS: "bitcos_gemv", FMT_TRIT5: "trit5_gemv", FMT_BIT2: "bit2_gem
 
 
 def _stream_handle(stream):
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    """The hipStream_t of `stream` (None: torch's current one) as an int.  The
+    current stream's handle is read directly where torch offers it: building a
+    torch Stream object for it takes 3 us, as long as the launch itself."""
+    if stream is not None:
+        return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    torch = _t()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def gemv(L: Layout, blob_dev, x, y, xscale=None, y_mode: int = Y_F32, stream=None):
@@ -197,7 +215,7 @@ def gemv(L: Layout, blob_dev, x, y, xscale=None, y_mode: int = Y_F32, stream=Non
     Y_I32_RAW_ADD) cuda tensor [m, n] (or [n]), overwritten or (the _ADD modes)
     added onto; xscale: None or float32 cuda tensor [m, k/128].
     """
-    import torch
+    torch = _t()
     m = x.shape[0] if x.dim() == 2 else 1
     if x.dtype == torch.int8:
         xd = X_I8
@@ -208,9 +226,10 @@ def gemv(L: Layout, blob_dev, x, y, xscale=None, y_mode: int = Y_F32, stream=Non
     for t, nm in ((blob_dev, "blob"), (x, "x"), (y, "y")):
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError(f"{nm} must be a contiguous cuda tensor")
+    k = L.k
     if blob_dev.dtype != torch.uint8 or blob_dev.numel() < L.total_bytes:
         raise ValueError("blob_dev must be uint8 with at least total_bytes elements")
-    if x.numel() != m * L.k:
+    if x.numel() != m * k:
         raise ValueError("x has the wrong size")
     want_y = torch.int32 if y_mode in (Y_I32_RAW, Y_I32_RAW_ADD) else torch.float32
     if y.dtype != want_y or y.numel() != m * L.n:
@@ -218,13 +237,14 @@ def gemv(L: Layout, blob_dev, x, y, xscale=None, y_mode: int = Y_F32, stream=Non
     xs_ptr = None
     if xscale is not None:
         if (not xscale.is_cuda or xscale.dtype != torch.float32 or not xscale.is_contiguous()
-                or xscale.numel() != m * (L.k // 128) or L.k % 128):
+                or xscale.numel() != m * (k // 128) or k % 128):
             raise ValueError("xscale must be a contiguous float32 cuda tensor [m, k/128]")
-        xs_ptr = ctypes.c_void_p(xscale.data_ptr())
-    fn = getattr(N.lib(), _GEMV[L.format])
-    st = fn(ctypes.byref(L), ctypes.c_void_p(blob_dev.data_ptr()), m, ctypes.c_void_p(x.data_ptr()), xd,
-            xs_ptr, ctypes.c_void_p(y.data_ptr()), y_mode, _stream_handle(stream))
-    N.check(st, _GEMV[L.format])
+        xs_ptr = xscale.data_ptr()
+    name = _GEMV[L.format]
+    st = getattr(N.lib(), name)(ctypes.byref(L), blob_dev.data_ptr(), m, x.data_ptr(), xd, xs_ptr, y.data_ptr(), y_mode,
+                                _stream_handle(stream))
+    if st:
+        N.check(st, name)
     return y
 
 
@@ -254,21 +274,21 @@ def add_partials(y, parts, stream=None):
     `stream`: the partial outputs of a split row's later column blocks.
     y: contiguous float32 cuda tensor of n elements; parts: contiguous float32
     cuda tensor [nparts, ...] of nparts * n elements."""
-    import torch
+    torch = _t()
     for t, nm in ((y, "y"), (parts, "parts")):
         if not t.is_cuda or not t.is_contiguous() or t.dtype != torch.float32:
             raise ValueError(f"{nm} must be a contiguous float32 cuda tensor")
     n = y.numel()
     if parts.dim() < 1 or parts.shape[0] < 1 or parts.numel() != parts.shape[0] * n:
         raise ValueError("parts must hold nparts slices of y's size")
-    N.check(N.lib().bitcos_add_partials(ctypes.c_void_p(y.data_ptr()), ctypes.c_void_p(parts.data_ptr()),
-                                        int(parts.shape[0]), n, _stream_handle(stream)), "bitcos_add_partials")
+    N.check(N.lib().bitcos_add_partials(y.data_ptr(), parts.data_ptr(), int(parts.shape[0]), n,
+                                        _stream_handle(stream)), "bitcos_add_partials")
     return y
 
 
 def quantize_activations(x, q, scale, stream=None):
     """Device int8 quantisation of bf16 activations per group of 128 (see bitcos.h)."""
-    import torch
+    torch = _t()
     if x.dtype != torch.bfloat16 or q.dtype != torch.int8 or scale.dtype != torch.float32:
         raise TypeError("x bfloat16, q int8, scale float32")
     for t in (x, q, scale):
@@ -278,8 +298,7 @@ def quantize_activations(x, q, scale, stream=None):
     k = x.numel() // m
     if q.numel() != m * k or scale.numel() != m * (k // 128) or k % 128:
         raise ValueError("q must be [m, k] and scale [m, k/128], k % 128 == 0")
-    N.check(N.lib().bitcos_quantize_act(ctypes.c_void_p(x.data_ptr()), m, k, ctypes.c_void_p(q.data_ptr()),
-                                        ctypes.c_void_p(scale.data_ptr()), _stream_handle(stream)),
+    N.check(N.lib().bitcos_quantize_act(x.data_ptr(), m, k, q.data_ptr(), scale.data_ptr(), _stream_handle(stream)),
             "bitcos_quantize_act")
     return q, scale
 
@@ -316,14 +335,16 @@ class Batch:
         self.host = np.zeros(nbytes, dtype=np.uint8)
         N.check(N.lib().bitcos_batch_build(count, m, arr, blobs, xp, sp, yp, x_dtype, y_mode,
                                            _ptr(self.host), nbytes), "bitcos_batch_build")
+        self._host_ptr = self.host.ctypes.data  # self.host is this object's own and never reallocated
         self.dev = torch.from_numpy(self.host).cuda()
         self.count = count
         self.m = m
         self._keep = (layouts, blobs_dev, xs, ys, xscales)
 
     def run(self, stream=None):
-        N.check(N.lib().bitcos_gemv_batch(_ptr(self.host), ctypes.c_void_p(self.dev.data_ptr()),
-                                          _stream_handle(stream)), "bitcos_gemv_batch")
+        st = N.lib().bitcos_gemv_batch(self._host_ptr, self.dev.data_ptr(), _stream_handle(stream))
+        if st:
+            N.check(st, "bitcos_gemv_batch")
 
 
 def _check_gemv_buffers(L, blob_dev, x, y, xscale, y_mode, m=1):

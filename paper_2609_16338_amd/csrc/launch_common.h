@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <mutex>
 #include <unordered_map>
 
@@ -33,15 +34,28 @@ inline int bitcos_blocks_per_cu(const void* fn, int threads) {
   return nb;
 }
 
+// Compute units of the current device; -1 on a HIP error.  Asked once per
+// device (a device property, as above).
+inline int bitcos_cus() {
+  constexpr int kDevices = 64;
+  static std::atomic<int> known[kDevices];
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return -1;
+  if (dev >= 0 && dev < kDevices) cus = known[dev].load(std::memory_order_relaxed);
+  if (cus > 0) return cus;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return -1;
+  if (dev >= 0 && dev < kDevices) known[dev].store(cus, std::memory_order_relaxed);
+  return cus;
+}
+
 // Blocks of `threads` threads for a persistent launch over `units` work units:
 // as many as the GPU keeps resident at once, no more than a wave per unit
 // needs, but at least a block on every CU while there are units for them
 // (the kernels spread a launch's units over all of its blocks).  -1 on a HIP
 // error.
 inline int64_t persistent_blocks(const void* fn, int64_t units, int threads = 256) {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return -1;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return -1;
+  const int cus = bitcos_cus();
+  if (cus < 1) return -1;
   const int64_t resident = static_cast<int64_t>(cus) * bitcos_blocks_per_cu(fn, threads);
   const int64_t wpb = threads / 64;
   int64_t need = (units + wpb - 1) / wpb;
