@@ -4,18 +4,25 @@
 //
 //   plan:  one wave per row counts its non-zeros (and flags values outside
 //          {-1, 0, 1}); one workgroup turns the counts into exclusive row
-//          offsets; the total is read back to size the sign section.
-//   pack:  the blob is zeroed; one wave per row walks the row's 32-weight
-//          words 64 at a time, writes each presence word, compacts the word's
-//          sign bits (negative weights among the present ones, in order) and
-//          ORs them into the sign stream at the row offset plus a wavefront
-//          prefix of the words' popcounts; then the unit offsets (row offsets
-//          at unit boundaries) and the scales (validated) are written.
+//          offsets and sums up the header.
+//   pack:  a first kernel writes what is not streams (unit offsets, validated
+//          scales, padding) and clears the sign dwords in which rows meet;
+//          then one wave per row walks the row's 32-weight words 64 at a
+//          time, writes each presence word, compacts the word's sign bits
+//          (negative weights among the present ones, in order) and joins them
+//          in LDS at the row offset plus a wavefront prefix of the words'
+//          popcounts, from where they are stored a dword at a time; only a
+//          row's first and last dwords, which its neighbours share, are ORed
+//          in memory.
+// Where everything goes follows from the non-zero count, so the call that
+// plans and packs at once (bitcos_pack_device_noalloc) reads the count back
+// only at the end: the pack kernels take it from the workspace and write
+// nothing if the plan failed or the blob would not fit.
 //
 // Workspace layout (caller device memory, bitcos_plan_device_workspace bytes):
-//   u32[0] value flag (weight outside {-1,0,1}, bad scale, or W changed
-//          between plan and pack), u32[1] unused, u64 at byte 8: nnz,
-//   u32[4 ..] row offsets, n + 1 entries.
+//   u32[0] value flag of the plan (weight outside {-1,0,1}), u32[1] value flag
+//   of the pack (bad scale, or W changed between plan and pack), u64 at byte
+//   8: nnz, u32[4 ..] row offsets, n + 1 entries.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -34,8 +41,8 @@ constexpr int kRowsPerBlock = 4;  // one wave per row
 constexpr int kScanThreads = 1024;
 
 struct WsHeader {
-  uint32_t flag;
-  uint32_t unused;
+  uint32_t plan_flag;
+  uint32_t pack_flag;
   uint64_t nnz;
 };
 static_assert(sizeof(WsHeader) == 16, "workspace header is 16 bytes");
@@ -44,35 +51,36 @@ __device__ __forceinline__ uint32_t* ws_rows(void* ws) {
   return reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(ws) + sizeof(WsHeader));
 }
 
-// Presence and negative masks of 4 weights (one dword of int8) at bits
-// [4 * part, 4 * part + 4); `bad` collects values outside {-1, 0, 1}.
-__device__ __forceinline__ void classify4(uint32_t v, int part, uint32_t& pres, uint32_t& neg, uint32_t& bad) {
-#pragma unroll
-  for (int b = 0; b < 4; ++b) {
-    const uint32_t byte = (v >> (8 * b)) & 0xFFu;
-    pres |= uint32_t(byte != 0u) << (4 * part + b);
-    neg |= uint32_t(byte == 0xFFu) << (4 * part + b);
-    bad |= uint32_t(byte != 0u && byte != 1u && byte != 0xFFu);
-  }
+// Presence and negative bytes of 8 weights (two dwords of int8).  A weight is
+// present where its bit 0 is set and negative where its bit 7 is; `bad`
+// collects where the byte is not the one those two bits name.
+__device__ __forceinline__ void classify8(uint32_t v0, uint32_t v1, uint32_t& pres, uint32_t& neg, uint32_t& bad) {
+  const uint32_t p0 = v0 & 0x01010101u, p1 = v1 & 0x01010101u;
+  const uint32_t n0 = (v0 >> 7) & 0x01010101u, n1 = (v1 >> 7) & 0x01010101u;
+  bad |= (v0 ^ (((n0 << 8) - n0) | p0)) | (v1 ^ (((n1 << 8) - n1) | p1));
+  pres = __builtin_amdgcn_udot4(p1, 0x80402010u, __builtin_amdgcn_udot4(p0, 0x08040201u, 0u, false), false);
+  neg = __builtin_amdgcn_udot4(n1, 0x80402010u, __builtin_amdgcn_udot4(n0, 0x08040201u, 0u, false), false);
 }
 
 // Presence / negative words of the 32 weights starting at weight 32 * word of
 // row `row` (zero past the end of the row or matrix).
 __device__ __forceinline__ void word_masks(rsrc_t rw, int row, int k, int word, uint32_t& pres,
                                            uint32_t& neg, uint32_t& bad) {
-  pres = 0;
-  neg = 0;
   const bool in = word < k / 32;
   const uint32_t off = in ? (static_cast<uint32_t>(row) * static_cast<uint32_t>(k) + 32u * word) : kOOB;
+  uint32_t p[4], n[4];
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
     const uint4 q = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw, off + 16u * c, 0, 0));
-    classify4(q.x, 4 * c + 0, pres, neg, bad);
-    classify4(q.y, 4 * c + 1, pres, neg, bad);
-    classify4(q.z, 4 * c + 2, pres, neg, bad);
-    classify4(q.w, 4 * c + 3, pres, neg, bad);
+    classify8(q.x, q.y, p[2 * c], n[2 * c], bad);
+    classify8(q.z, q.w, p[2 * c + 1], n[2 * c + 1], bad);
   }
+  pres = p[0] | p[1] << 8 | p[2] << 16 | p[3] << 24;
+  neg = n[0] | n[1] << 8 | n[2] << 16 | n[3] << 24;
 }
+
+// A row's count; its top bit says that the row holds a bad value (k < 2^31).
+constexpr uint32_t kBadRow = 0x80000000u;
 
 __global__ void __launch_bounds__(kRowsPerBlock * kWave) count_rows_kernel(const int8_t* w, int n, int k, void* ws) {
   const int lane = threadIdx.x & 63;
@@ -86,103 +94,209 @@ __global__ void __launch_bounds__(kRowsPerBlock * kWave) count_rows_kernel(const
     cnt += __builtin_popcount(pres);
   }
   const int tot = seg_sum<64>(static_cast<int>(cnt));
-  if (lane == 63) ws_rows(ws)[row] = static_cast<uint32_t>(tot);
-  if (bad) atomicOr(&static_cast<WsHeader*>(ws)->flag, 1u);
+  const bool any_bad = __any(bad != 0u);
+  if (lane == 63) ws_rows(ws)[row] = static_cast<uint32_t>(tot) | (any_bad ? kBadRow : 0u);
 }
 
-// Exclusive scan of the n row counts in place (row offsets), total into the
-// header and row n.  One workgroup; each thread owns a contiguous slice.
+// Exclusive scan of the n row counts in place (row offsets), the total into
+// row n and the whole header.  One workgroup; four rows per thread and pass
+// (n k < 2^31: 32 bits hold every sum).
 __global__ void __launch_bounds__(kScanThreads) scan_rows_kernel(int n, void* ws) {
-  __shared__ uint64_t part[kScanThreads];
+  constexpr int kWaves = kScanThreads / kWave;
+  __shared__ uint32_t part[kWaves];
+  __shared__ uint32_t any_bad;
   uint32_t* rows = ws_rows(ws);
-  const int t = threadIdx.x;
-  const int per = (n + kScanThreads - 1) / kScanThreads;
-  const int lo = min(n, t * per), hi = min(n, lo + per);
-  uint64_t s = 0;
-  for (int i = lo; i < hi; ++i) s += rows[i];
-  part[t] = s;
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  if (t == 0) any_bad = 0;
+  uint32_t run = 0, bad = 0;
+  for (int base = 0; base < n; base += 4 * kScanThreads) {
+    const int i0 = base + 4 * t;
+    uint32_t c[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      c[i] = i0 + i < n ? rows[i0 + i] : 0u;
+      bad |= c[i] & kBadRow;
+      c[i] &= ~kBadRow;
+    }
+    const uint32_t s = c[0] + c[1] + c[2] + c[3];
+    const uint32_t incl = static_cast<uint32_t>(wave_incl_scan(static_cast<int>(s)));
+    __syncthreads();  // the previous pass has read `part`
+    if (lane == 63) part[wv] = incl;
+    __syncthreads();
+    uint32_t before = run;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) {
+      before += i < wv ? part[i] : 0u;
+      run += part[i];
+    }
+    uint32_t at = before + incl - s;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i0 + i < n) rows[i0 + i] = at;
+      at += c[i];
+    }
+  }
+  if (bad) atomicOr(&any_bad, 1u);
   __syncthreads();
-  for (int d = 1; d < kScanThreads; d <<= 1) {  // inclusive Hillis-Steele scan
-    const uint64_t v = t >= d ? part[t - d] : 0;
-    __syncthreads();
-    part[t] += v;
-    __syncthreads();
-  }
-  uint64_t run = part[t] - s;  // exclusive prefix of this slice
-  for (int i = lo; i < hi; ++i) {
-    const uint32_t c = rows[i];
-    rows[i] = static_cast<uint32_t>(run);
-    run += c;
-  }
-  if (t == kScanThreads - 1) {
-    const uint64_t total = part[t];
-    static_cast<WsHeader*>(ws)->nnz = total;
-    rows[n] = static_cast<uint32_t>(total);
+  if (t == 0) {
+    WsHeader* h = static_cast<WsHeader*>(ws);
+    h->plan_flag = any_bad;
+    h->pack_flag = 0;
+    h->nnz = run;
+    rows[n] = run;
   }
 }
 
-// Compact the sign bits of the present weights of one word, in order.
+// The sign bits `neg` of the present weights `pres` of one word, compacted in
+// order: the parallel-suffix compress of Warren, "Hacker's Delight" (7-4),
+// five rounds that each move the bits whose distance has that power of two.
 __device__ __forceinline__ uint32_t compact_signs(uint32_t pres, uint32_t neg) {
-  uint32_t out = 0;
-  int q = 0;
-  while (pres) {
-    const int b = __builtin_ctz(pres);
-    out |= ((neg >> b) & 1u) << q;
-    ++q;
-    pres &= pres - 1u;
+  uint32_t x = neg & pres, m = pres;
+  uint32_t mk = ~m << 1;
+#pragma unroll
+  for (int i = 0; i < 5; ++i) {
+    uint32_t mp = mk ^ (mk << 1);
+    mp ^= mp << 2;
+    mp ^= mp << 4;
+    mp ^= mp << 8;
+    mp ^= mp << 16;
+    const uint32_t mv = mp & m;
+    m = (m ^ mv) | (mv >> (1 << i));
+    const uint32_t t = x & mv;
+    x = (x ^ t) | (t >> (1 << i));
+    mk &= ~mp;
   }
-  return out;
+  return x;
 }
 
-__global__ void __launch_bounds__(kRowsPerBlock * kWave)
-    pack_rows_kernel(const int8_t* w, int n, int k, void* ws, uint32_t* bitmap, uint32_t* signs, uint64_t nnz) {
+// What the pack kernels write to.  The sections after the signs start where
+// the non-zero count puts them: `nnz`, or with from_ws the plan's in the
+// workspace, and then only if the plan found no bad value and the blob fits.
+struct PackTarget {
+  uint8_t* dst;
+  uint64_t cap;
+  uint64_t off_signs;
+  uint64_t nnz;
+  int64_t ns;
+  int n, k, unit_rows, units;
+  bool from_ws;
+};
+struct Sections {
+  uint64_t nnz, signs_end, off_offsets, off_scales, total;  // signs_end: of the stream, without its padding
+  bool ok;
+};
+__host__ __device__ __forceinline__ uint64_t align256(uint64_t v) { return (v + 255u) & ~uint64_t(255); }
+constexpr uint64_t kSignPad = 16;  // zero bytes after the sign stream
+__device__ __forceinline__ Sections sections(const PackTarget& p, const void* ws) {
+  Sections s;
+  const WsHeader* h = static_cast<const WsHeader*>(ws);
+  s.nnz = p.from_ws ? h->nnz : p.nnz;
+  s.signs_end = p.off_signs + (s.nnz + 31) / 32 * 4;
+  s.off_offsets = align256(s.signs_end + kSignPad);
+  s.off_scales = align256(s.off_offsets + 4u * (static_cast<uint64_t>(p.units) + 1));
+  s.total = align256(s.off_scales + 2u * static_cast<uint64_t>(p.ns));
+  s.ok = !p.from_ws || (h->plan_flag == 0 && s.total <= p.cap);
+  return s;
+}
+
+// Unit offsets, scales, zero padding, and zeros in the sign dwords that hold
+// a row's first bit (which rows may share).
+constexpr int kSideThreads = 256;
+__global__ void __launch_bounds__(kSideThreads) pack_side_kernel(const uint16_t* scales, PackTarget p, void* ws) {
+  const Sections s = sections(p, ws);
+  if (!s.ok) return;
+  const uint32_t* rows = ws_rows(ws);
+  uint32_t* signs = reinterpret_cast<uint32_t*>(p.dst + p.off_signs);
+  uint32_t* offsets = reinterpret_cast<uint32_t*>(p.dst + s.off_offsets);
+  uint16_t* out = reinterpret_cast<uint16_t*>(p.dst + s.off_scales);
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kSideThreads;
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * kSideThreads + threadIdx.x;
+  for (int64_t i = t; i <= p.n; i += stride) {
+    const uint32_t at = rows[i];
+    if (at <= s.nnz) signs[at >> 5] = 0;
+  }
+  for (int64_t u = t; u <= p.units; u += stride)
+    offsets[u] = rows[u * p.unit_rows < p.n ? u * p.unit_rows : p.n];
+  bool bad = false;
+  for (int64_t i = t; i < p.ns; i += stride) {
+    const uint16_t h = scales[i];
+    out[i] = h;
+    bad |= (h & 0x8000u) || (h & 0x7C00u) == 0x7C00u;
+  }
+  if (bad) atomicOr(&static_cast<WsHeader*>(ws)->pack_flag, 1u);
+  if (blockIdx.x == 0) {
+    const auto clear = [&](uint64_t from, uint64_t to) {  // 2-byte steps: scales may end at an odd one
+      for (uint64_t i = from + 2u * threadIdx.x; i < to; i += 2u * kSideThreads)
+        *reinterpret_cast<uint16_t*>(p.dst + i) = 0;
+    };
+    clear(static_cast<uint64_t>(p.n) * static_cast<uint64_t>(p.k) / 8, p.off_signs);
+    clear(s.signs_end, s.off_offsets);
+    clear(s.off_offsets + 4u * (static_cast<uint64_t>(p.units) + 1), s.off_scales);
+    clear(s.off_scales + 2u * static_cast<uint64_t>(p.ns), s.total);
+  }
+}
+
+// Presence words and signs of one row per wave.  A pass's sign bits (at most
+// 64 x 32, starting anywhere in a dword) are ORed together in LDS; dwords the
+// row has to itself are stored, the others ORed (two atomics per row; ORing
+// every word's bits into memory took 22 us of a 5120 x 5120 pack, this 10.5:
+// 26 MB read and 6 MB written at 3.1 TB/s).
+__global__ void __launch_bounds__(kRowsPerBlock * kWave) pack_rows_kernel(const int8_t* w, PackTarget p, void* ws) {
+  __shared__ uint32_t bits[kRowsPerBlock][kWave + 1];
   const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
-  if (row >= n) return;  // whole wave
+  const int wv = threadIdx.x >> 6;
+  const int row = blockIdx.x * kRowsPerBlock + wv;
+  const Sections s = sections(p, ws);
+  if (row >= p.n || !s.ok) return;  // whole wave
+  uint32_t* bitmap = reinterpret_cast<uint32_t*>(p.dst);
+  uint32_t* signs = reinterpret_cast<uint32_t*>(p.dst + p.off_signs);
   const uint32_t* rows = ws_rows(ws);
   const uint32_t start = rows[row], end = rows[row + 1];
-  const rsrc_t rw = make_rsrc(w, static_cast<uint32_t>(n) * static_cast<uint32_t>(k));
-  const int upr = k / 32;
-  uint32_t carry = start, bad = 0;
+  const rsrc_t rw = make_rsrc(w, static_cast<uint32_t>(p.n) * static_cast<uint32_t>(p.k));
+  const int upr = p.k / 32;
+  // The planned row range bounds every write (W changed since the plan:
+  // flagged, nothing written outside the row's range).
+  const bool planned = start <= end && end <= s.nnz;
+  uint32_t carry = start, bad = planned ? 0u : 1u;
+  uint32_t left = 0;  // the row's bits in the dword that `carry` points into
   for (int w0 = 0; w0 < upr; w0 += kWave) {
     const int word = w0 + lane;
     uint32_t pres, neg;
-    word_masks(rw, row, k, word, pres, neg, bad);
-    const int pc = __builtin_popcount(pres);
-    const int incl = wave_incl_scan(pc);
-    const uint32_t pos = carry + static_cast<uint32_t>(incl - pc);
-    carry += static_cast<uint32_t>(lane63(incl));
+    word_masks(rw, row, p.k, word, pres, neg, bad);
+    const uint32_t pc = static_cast<uint32_t>(__builtin_popcount(pres));
+    const uint32_t incl = static_cast<uint32_t>(wave_incl_scan(static_cast<int>(pc)));
+    const uint32_t pos = carry + incl - pc;
+    const uint32_t base = carry >> 5;  // the pass's first dword
+    carry += static_cast<uint32_t>(lane63(static_cast<int>(incl)));
     if (word < upr) bitmap[static_cast<size_t>(row) * upr + word] = pres;
-    // The planned row range bounds every write (W changed since the plan:
-    // flagged, nothing written outside the row's range).
-    if (pc > 0 && pos + static_cast<uint32_t>(pc) <= end && end <= nnz) {
+    bits[wv][lane] = lane == 0 ? left : 0u;
+    if (lane == 0) bits[wv][kWave] = 0;
+    __builtin_amdgcn_wave_barrier();
+    if (pc > 0 && planned && pos + pc <= end) {
       const uint32_t cs = compact_signs(pres, neg);
-      const uint32_t d = pos >> 5, sh = pos & 31u;
-      if (cs) {
-        atomicOr(&signs[d], cs << sh);
-        if (sh + static_cast<uint32_t>(pc) > 32u) atomicOr(&signs[d + 1], cs >> (32u - sh));
-      }
+      const uint32_t d = (pos >> 5) - base, sh = pos & 31u;  // d <= 63
+      atomicOr(&bits[wv][d], cs << sh);
+      if (sh + pc > 32u) atomicOr(&bits[wv][d + 1], cs >> (32u - sh));
     } else if (pc > 0) {
       bad = 1;
     }
+    __builtin_amdgcn_wave_barrier();
+    // The dwords this pass completes; the one it ends in waits for the next.
+    const uint32_t done = (carry >> 5) - base;  // <= 64
+    left = bits[wv][done];
+    const uint32_t at = base + static_cast<uint32_t>(lane);
+    if (planned && static_cast<uint32_t>(lane) < done && (at << 5) < end) {
+      const uint32_t v = bits[wv][lane];
+      if ((at << 5) >= start && (at << 5) + 32u <= end)
+        signs[at] = v;
+      else if (v)
+        atomicOr(&signs[at], v);
+    }
+    __builtin_amdgcn_wave_barrier();
   }
+  if (lane == 0 && planned && left && ((carry >> 5) << 5) < end) atomicOr(&signs[carry >> 5], left);
   if (lane == 63 && carry != end) bad = 1;
-  if (bad) atomicOr(&static_cast<WsHeader*>(ws)->flag, 1u);
-}
-
-__global__ void offsets_kernel(const void* ws, int n, int unit_rows, int units, uint32_t* offsets) {
-  const int u = blockIdx.x * blockDim.x + threadIdx.x;
-  if (u > units) return;
-  const uint32_t* rows = reinterpret_cast<const uint32_t*>(static_cast<const uint8_t*>(ws) + sizeof(WsHeader));
-  offsets[u] = rows[min(static_cast<int64_t>(u) * unit_rows, static_cast<int64_t>(n))];
-}
-
-__global__ void scales_kernel(const uint16_t* src, int64_t count, uint16_t* dst, void* ws) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= count) return;
-  const uint16_t h = src[i];
-  dst[i] = h;
-  if ((h & 0x8000u) || (h & 0x7C00u) == 0x7C00u) atomicOr(&static_cast<WsHeader*>(ws)->flag, 1u);
+  if (bad) atomicOr(&static_cast<WsHeader*>(ws)->pack_flag, 1u);
 }
 
 int check_shape(int32_t n, int32_t k, int32_t group, int32_t unit_rows) {
@@ -197,6 +311,42 @@ int sync_status(hipStream_t st) {
   if (hipGetLastError() != hipSuccess) return BITCOS_E_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return BITCOS_E_HIP;
   return BITCOS_OK;
+}
+
+// Enqueues the plan: row offsets and header into the workspace.
+void launch_plan(const int8_t* w, int n, int k, void* ws, hipStream_t s) {
+  const unsigned blocks = static_cast<unsigned>((n + kRowsPerBlock - 1) / kRowsPerBlock);
+  hipLaunchKernelGGL(count_rows_kernel, dim3(blocks), dim3(kRowsPerBlock * kWave), 0, s, w, n, k, ws);
+  hipLaunchKernelGGL(scan_rows_kernel, dim3(1), dim3(kScanThreads), 0, s, n, ws);
+}
+
+// Enqueues the pack of a planned matrix into dst; L: its layout, or with
+// from_ws the layout of any count (the kernels take the plan's).
+void launch_pack(const int8_t* w, const uint16_t* scales, const bitcos_layout& L, void* dst, size_t cap, bool from_ws,
+                 void* ws, hipStream_t s) {
+  PackTarget p;
+  p.dst = static_cast<uint8_t*>(dst);
+  p.cap = cap;
+  p.off_signs = L.sec_off[BITCOS_SEC_SIGNS];
+  p.nnz = L.nnz;
+  p.ns = L.group == 128 ? static_cast<int64_t>(L.n) * (L.k / 128) : 1;
+  p.n = L.n;
+  p.k = L.k;
+  p.unit_rows = L.unit_rows;
+  p.units = static_cast<int>((static_cast<int64_t>(L.n) + L.unit_rows - 1) / L.unit_rows);
+  p.from_ws = from_ws;
+  const int64_t most = p.ns > p.n + 1 ? p.ns : p.n + 1;
+  const int64_t side = (most + kSideThreads - 1) / kSideThreads;
+  hipLaunchKernelGGL(pack_side_kernel, dim3(static_cast<unsigned>(side < 1024 ? side : 1024)), dim3(kSideThreads), 0,
+                     s, scales, p, ws);
+  hipLaunchKernelGGL(pack_rows_kernel, dim3(static_cast<unsigned>((p.n + kRowsPerBlock - 1) / kRowsPerBlock)),
+                     dim3(kRowsPerBlock * kWave), 0, s, w, p, ws);
+}
+
+// Reads the workspace header back and waits for the stream.
+int read_header(WsHeader* h, const void* ws, hipStream_t s) {
+  if (hipMemcpyAsync(h, ws, sizeof(*h), hipMemcpyDeviceToHost, s) != hipSuccess) return BITCOS_E_HIP;
+  return sync_status(s);
 }
 
 // Workspace of bitcos_pack_device_noalloc for matrices of up to
@@ -242,15 +392,11 @@ int bitcos_plan_device(const int8_t* w_dev, int32_t n, int32_t k, int32_t group,
   if (st) return st;
   if (ws_bytes < bitcos_plan_device_workspace(n)) return BITCOS_E_SPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (hipMemsetAsync(ws_dev, 0, sizeof(WsHeader), s) != hipSuccess) return BITCOS_E_HIP;
-  const unsigned blocks = static_cast<unsigned>((n + kRowsPerBlock - 1) / kRowsPerBlock);
-  hipLaunchKernelGGL(count_rows_kernel, dim3(blocks), dim3(kRowsPerBlock * kWave), 0, s, w_dev, n, k, ws_dev);
-  hipLaunchKernelGGL(scan_rows_kernel, dim3(1), dim3(kScanThreads), 0, s, n, ws_dev);
+  launch_plan(w_dev, n, k, ws_dev, s);
   WsHeader h;
-  if (hipMemcpyAsync(&h, ws_dev, sizeof(h), hipMemcpyDeviceToHost, s) != hipSuccess) return BITCOS_E_HIP;
-  st = sync_status(s);
+  st = read_header(&h, ws_dev, s);
   if (st) return st;
-  if (h.flag) return BITCOS_E_VALUE;
+  if (h.plan_flag) return BITCOS_E_VALUE;
   return bitcos::bitcos_layout_for(n, k, group, unit_rows, h.nnz, out);
 }
 
@@ -268,25 +414,13 @@ int bitcos_pack_device(const int8_t* w_dev, const uint16_t* scales_dev, const bi
   if (st || chk.total_bytes != L->total_bytes || chk.sec_off[BITCOS_SEC_SCALES] != L->sec_off[BITCOS_SEC_SCALES])
     return BITCOS_E_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  uint8_t* blob = static_cast<uint8_t*>(dst_dev);
-  if (hipMemsetAsync(blob, 0, L->total_bytes, s) != hipSuccess) return BITCOS_E_HIP;
-  if (hipMemsetAsync(ws_dev, 0, sizeof(uint32_t), s) != hipSuccess) return BITCOS_E_HIP;  // value flag
-  const int n = L->n, k = L->k;
-  const unsigned blocks = static_cast<unsigned>((n + kRowsPerBlock - 1) / kRowsPerBlock);
-  hipLaunchKernelGGL(pack_rows_kernel, dim3(blocks), dim3(kRowsPerBlock * kWave), 0, s, w_dev, n, k, ws_dev,
-                     reinterpret_cast<uint32_t*>(blob + L->sec_off[BITCOS_SEC_BITMAP]),
-                     reinterpret_cast<uint32_t*>(blob + L->sec_off[BITCOS_SEC_SIGNS]), L->nnz);
-  const int units = (n + L->unit_rows - 1) / L->unit_rows;
-  hipLaunchKernelGGL(offsets_kernel, dim3((units + 1 + 255) / 256), dim3(256), 0, s, ws_dev, n, L->unit_rows, units,
-                     reinterpret_cast<uint32_t*>(blob + L->sec_off[BITCOS_SEC_OFFSETS]));
-  const int64_t ns = L->group == 128 ? static_cast<int64_t>(n) * (k / 128) : 1;
-  hipLaunchKernelGGL(scales_kernel, dim3(static_cast<unsigned>((ns + 255) / 256)), dim3(256), 0, s, scales_dev, ns,
-                     reinterpret_cast<uint16_t*>(blob + L->sec_off[BITCOS_SEC_SCALES]), ws_dev);
-  uint32_t flag = 0;
-  if (hipMemcpyAsync(&flag, ws_dev, sizeof(flag), hipMemcpyDeviceToHost, s) != hipSuccess) return BITCOS_E_HIP;
-  st = sync_status(s);
+  if (hipMemsetAsync(&static_cast<WsHeader*>(ws_dev)->pack_flag, 0, sizeof(uint32_t), s) != hipSuccess)
+    return BITCOS_E_HIP;
+  launch_pack(w_dev, scales_dev, chk, dst_dev, cap, false, ws_dev, s);
+  WsHeader h;
+  st = read_header(&h, ws_dev, s);
   if (st) return st;
-  return flag ? BITCOS_E_VALUE : BITCOS_OK;
+  return h.pack_flag ? BITCOS_E_VALUE : BITCOS_OK;
 }
 
 int bitcos_pack_device_noalloc(const int8_t* w_dev, const uint16_t* scales_dev, int32_t n, int32_t k,
@@ -299,11 +433,22 @@ int bitcos_pack_device_noalloc(const int8_t* w_dev, const uint16_t* scales_dev, 
   void* ws = nullptr;
   st = noalloc_workspace(&ws);
   if (st) return st;
-  const size_t ws_bytes = bitcos_plan_device_workspace(n);
-  st = bitcos_plan_device(w_dev, n, k, group, unit_rows, ws, ws_bytes, out, stream);
+  // The sections' places for any count but the sign stream's length: the
+  // kernels work out the rest from the count in the workspace.
+  bitcos_layout base;
+  st = bitcos::bitcos_layout_for(n, k, group, unit_rows, 0, &base);
+  if (st) return st;
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  launch_plan(w_dev, n, k, ws, s);
+  launch_pack(w_dev, scales_dev, base, dst_dev, cap, true, ws, s);
+  WsHeader h;
+  st = read_header(&h, ws, s);
+  if (st) return st;
+  if (h.plan_flag) return BITCOS_E_VALUE;
+  st = bitcos::bitcos_layout_for(n, k, group, unit_rows, h.nnz, out);
   if (st) return st;
   if (cap < out->total_bytes) return BITCOS_E_SPACE;  // *out tells the caller the size
-  return bitcos_pack_device(w_dev, scales_dev, out, ws, ws_bytes, dst_dev, cap, stream);
+  return h.pack_flag ? BITCOS_E_VALUE : BITCOS_OK;
 }
 
 }  // extern "C"
