@@ -160,9 +160,10 @@ int bitcos_unpack(const bitcos_layout* L, const void* blob, size_t blob_bytes, i
  *             decoded weight multiplied against all m rows on the matrix
  *             cores) when the layout has one sign offset per row and
  *             k % 128 == 0; other layouts run m batch-1 launches.  At m = 1
- *             rows longer than the batch-1 kernels take (bf16 k > 16384,
- *             int8 k > 32768) run the small-batch kernel too, with such
- *             layouts; others return E_UNSUPPORTED.
+ *             rows longer than a batch-1 tile (bf16 k > 16384, int8
+ *             k > 32768) run, with such layouts, a batch-1 kernel with two
+ *             waves per row (up to twice that k) or the small-batch kernel;
+ *             other layouts return E_UNSUPPORTED.
  *   x_dev     device activations [m][k]: int8 (BITCOS_X_I8) or bf16 bits
  *             (BITCOS_X_BF16), row-major.
  *   xscale_dev  NULL (a = 1) or device fp32 [m][k/128] per-group activation
@@ -321,7 +322,9 @@ int bitcos_pack_device_noalloc(const int8_t* w_dev, const uint16_t* scales_dev, 
 
 /* ---- launch description (for measurement) ---------------------------------
  * Fills the kernel configuration a GEMV on this layout would launch with,
- * for a call (or a batch of such layouts) without activation scales: words
+ * for a call (or a batch of such layouts) without activation scales (rows
+ * longer than a batch-1 tile: what a batch launches; a single call may take
+ * the batch-1 kernel with two waves per row instead): words
  * (or blocks) per lane, lanes per row segment, rows per wave step, waves and
  * workgroups, and which kernel runs (BITCOS_KERNEL_*).  Errors as for the
  * GEMV. */

@@ -35,7 +35,11 @@ constexpr int fast_waves_per_simd(int w, bool bf16) {
 }
 constexpr int fast_threads(int w, bool bf16) { return 256 * fast_waves_per_simd(w, bf16); }
 
-template <int W, bool BF16>
+// Rows longer than a tile, one GEMV: two waves of a workgroup share a row (see
+// below); their sums of up to this many rows of the workgroup meet in LDS.
+constexpr int kLongRows = 512;
+
+template <int W, bool BF16, bool LONG = false>
 struct FastCfg {
   // Prefetch ring depth: one step ahead.  Two steps ahead (which fits the
   // int8 tiles up to five words per lane) measured no faster.
@@ -53,7 +57,9 @@ struct FastCfg {
   // Sign-table copies: 32 (a conflict-free 8-byte lookup for any 32 keys)
   // when the tables and stage buffers fit the LDS, else 16, else 8.
   static constexpr int kWaves = fast_threads(W, BF16) / 64;
-  static constexpr int lds_bytes(int ct) { return 65536 + 2048 * ct + kStages * kWaves * kStageBytes; }
+  static constexpr int lds_bytes(int ct) {
+    return 65536 + 2048 * ct + kStages * kWaves * kStageBytes + (LONG ? 8 * kLongRows : 0);
+  }
   static constexpr int kSignCopies = lds_bytes(32) <= kLdsBytes ? 32 : lds_bytes(16) <= kLdsBytes ? 16 : 8;
   static_assert(lds_bytes(kSignCopies) <= kLdsBytes, "streaming kernel LDS");
 };
@@ -108,15 +114,27 @@ struct FastGen {
   }
 };
 
-template <int W, int SEG, bool BF16, bool TABLE>
+// LONG: rows of 64 W .. 128 W words, too long for one wave's registers (one
+// GEMV, 64 lanes per row).  Waves 2t and 2t + 1 of a workgroup take the first
+// 64 W words and the rest of the same rows.  A row's signs lie between two
+// stored offsets, so the first wave counts its cursor from the row's start
+// and the second from its end, and neither waits for the other: each fetches
+// the signs its words could have at most (what it fetches too much the other
+// wave needs, and the L2 serves it once).  The two sums of a row meet in LDS
+// after the last step.  5120 x 25600 bf16: 17 us, 31 on the small-batch
+// kernel with each unit's K split over 8 waves.
+template <int W, int SEG, bool BF16, bool TABLE, bool LONG = false>
 __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(const KernelArgs a) {
   constexpr int R = kWave / SEG;
   constexpr int NX = BF16 ? 16 : 8;
   constexpr int NT = fast_threads(W, BF16);
   constexpr int WPB = NT / kWave;
-  constexpr int D = FastCfg<W, BF16>::kStages;
-  constexpr int NSC = FastCfg<W, BF16>::kSignChunks;
-  constexpr int SCR = FastCfg<W, BF16>::kScratchDw;
+  using Cfg = FastCfg<W, BF16, LONG>;
+  constexpr int D = Cfg::kStages;
+  constexpr int NSC = Cfg::kSignChunks;
+  constexpr int SCR = Cfg::kScratchDw;
+  static_assert(!LONG || (SEG == 64 && !TABLE), "long rows: one row per step, one GEMV");
+  constexpr int PARTS = LONG ? 2 : 1;  // waves that share a row
   using Acc = typename std::conditional<BF16, float, int>::type;
   using Ends = GroupEnds<W, 4>;
   constexpr int NQ = Ends::kNQ;
@@ -125,8 +143,9 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   // SCR dwords of every buffer).  The stage buffers are separate objects so
   // the compiler can tell that a read of one does not wait on the fetch into
   // another.
-  constexpr int CT = FastCfg<W, BF16>::kSignCopies;
+  constexpr int CT = Cfg::kSignCopies;
   __shared__ FastTables<BF16, CT> tab;
+  __shared__ uint32_t part_sums[LONG ? 2 * kLongRows : 1];
   __shared__ uint4 sbuf0[WPB * SCR / 4];
   __shared__ uint4 sbuf1[WPB * SCR / 4];
   __shared__ uint4 sbuf2[D > 2 ? WPB * SCR / 4 : 1];
@@ -141,11 +160,12 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int total = static_cast<int>(a.total_units);
-  const auto range = unit_range<WPB>(total, wv);
+  const auto range = unit_range<WPB / PARTS>(total, wv / PARTS);
+  const int part = LONG ? wv & 1 : 0;
 
   const int rho = lane / SEG;
   const int j = lane % SEG;
-  const int w0 = j * W;
+  const int w0 = (part * SEG + j) * W;
   const int ph = Ends::kAligned ? 0 : (w0 & 3);
   const int g0 = w0 >> 2;
   const FastLane fl = fast_lane<BF16, CT>(lane);
@@ -221,7 +241,13 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   };
   auto issue_signs = [&](auto stage_c) {
     constexpr int k = decltype(stage_c)::value;
-    const FastStep& s = st[k];
+    FastStep& s = st[k];
+    if constexpr (LONG) {  // the most signs this wave's words can have, from the end it counts from
+      const uint32_t most = 32u * static_cast<uint32_t>(part ? max(a.one.upr - SEG * W, 0) : SEG * W);
+      if (s.off1 - s.off0 > most) {
+        if (part) s.off0 = s.off1 - most; else s.off1 = s.off0 + most;
+      }
+    }
     // The step's sign block: dwords [off0 / 32, off1 / 32 + 1] are the most
     // any window reads.  Only the 16-byte pieces of that range are fetched,
     // straight into this wave's part of the stage buffer (lane l of chunk c
@@ -258,7 +284,7 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     xdi = d;
     const auto& g = desc_at<TABLE>(a, d);
     nwl = g.upr - w0;
-    ragged = g.upr != SEG * W;
+    ragged = g.upr != PARTS * SEG * W;
     mode = g.mode;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
@@ -342,7 +368,9 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
       cnt += __builtin_popcount(Pw[w]);
     }
     const int incl = wave_incl_scan(cnt);
-    const uint32_t base = stage_bits + wave_bits + (s.off0 & 31u) + static_cast<uint32_t>(incl - cnt);
+    uint32_t first = s.off0 & 31u;
+    if (LONG && part) first = s.off1 - (s.off0 & ~31u) - static_cast<uint32_t>(lane63(incl));
+    const uint32_t base = stage_bits + wave_bits + first + static_cast<uint32_t>(incl - cnt);
     __builtin_amdgcn_wave_barrier();
     // Decode burst at raised wave priority (as in the matrix-core kernel).
     __builtin_amdgcn_s_setprio(1);
@@ -356,7 +384,7 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
       LdsU32* wp = (LdsU32*)static_cast<size_t>((b >> 3) & ~3u);
       return __builtin_amdgcn_alignbit(wp[1], wp[0], b);
     };
-    if constexpr (FastCfg<W, BF16>::kPipelined) {
+    if constexpr (Cfg::kPipelined) {
       Look<BF16> L = look(Pw[0], window(0), fl);
 #pragma unroll
       for (int w = 0; w < W; ++w) {
@@ -389,6 +417,11 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
 
     // One lane per row stores; rows past the end are outside ry and dropped.
     const uint32_t soff_y = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(s.row0) * 4u);
+    if (LONG && ((!BF16 && (mode & kModeRaw)) || !(mode & (kModeGrouped | kModeXscale)))) {  // scaled, if at all, with the other wave's
+      const Acc tot = seg_sum<SEG>(run[W - 1]);
+      if (j == SEG - 1) part_sums[part * kLongRows + s.row0 - range.first] = __builtin_bit_cast(uint32_t, tot);
+      return;
+    }
     if (!BF16 && (mode & kModeRaw)) {
       const int tot = seg_sum<SEG>(static_cast<int>(run[W - 1]));
       pend = j == SEG - 1;
@@ -398,12 +431,12 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
       pend_ry = ry;
       return;
     }
-    float part;
+    float rsum;
     if (!(mode & (kModeGrouped | kModeXscale))) {
       if constexpr (BF16) {
-        part = tensor_scale * (2.0f * seg_sum<SEG>(static_cast<float>(run[W - 1])));
+        rsum = tensor_scale * (2.0f * seg_sum<SEG>(static_cast<float>(run[W - 1])));
       } else {
-        part = tensor_scale * static_cast<float>(seg_sum<SEG>(static_cast<int>(run[W - 1])));
+        rsum = tensor_scale * static_cast<float>(seg_sum<SEG>(static_cast<int>(run[W - 1])));
       }
     } else {
       float f = 0.0f;
@@ -416,10 +449,14 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
         const float sc = (mode & kModeGrouped) ? half_bits_to_float(SC[k][q]) : tensor_scale;
         f += sc * xs[q] * static_cast<float>(grp);
       }
-      part = seg_sum<SEG>(BF16 ? 2.0f * f : f);
+      rsum = seg_sum<SEG>(BF16 ? 2.0f * f : f);
+      if constexpr (LONG) {
+        if (j == SEG - 1) part_sums[part * kLongRows + s.row0 - range.first] = __builtin_bit_cast(uint32_t, rsum);
+        return;
+      }
     }
     pend = j == SEG - 1;
-    pend_bits = __builtin_bit_cast(uint32_t, part);
+    pend_bits = __builtin_bit_cast(uint32_t, rsum);
     pend_soff = soff_y;
     pend_mode = mode;
     pend_ry = ry;
@@ -431,7 +468,7 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   // activations loads its own when it decodes its first step.
   static_assert(D == 2, "one step in flight before the loop");
   st[0] = gen.next(a);
-  FirstX<W * NX / 4, SEG, NT, WPB * SCR / 4> fx;
+  FirstX<W * NX / 4, PARTS * SEG, NT, WPB * SCR / 4> fx;
   {
     const auto& g = desc_at<TABLE>(a, fdi);
     fx.fetch(make_rsrc(g.x, g.x_bytes), threadIdx.x);
@@ -447,7 +484,7 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
       shared = g.x == f.x && g.x_bytes == f.x_bytes;
     }
   }
-  fx.share(reinterpret_cast<piece_t*>(sbuf1), threadIdx.x, j, shared && st[0].valid, xr);
+  fx.share(reinterpret_cast<piece_t*>(sbuf1), threadIdx.x, part * SEG + j, shared && st[0].valid, xr);
   if (!shared) xdi = -1;
 
   bool more = true;
@@ -471,6 +508,26 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     }(std::make_integer_sequence<int, D>{});
   }
   flush_store();
+  if constexpr (LONG) {
+    __syncthreads();
+    const GemvDesc& g = a.one;
+    const int rows = min(kLongRows, static_cast<int>(unit_range<1>(total, 0).end - range.first));
+    const bool raw = !BF16 && (g.mode & kModeRaw);
+    const bool ints = !BF16 && (raw || !(g.mode & (kModeGrouped | kModeXscale)));
+    const float sc = half_bits_to_float(gp_u16(g.scales)[0]);
+    const rsrc_t rout = make_rsrc(g.y, g.y_bytes);
+    for (int r = threadIdx.x; r < rows; r += NT) {
+      const uint32_t p0 = part_sums[r], p1 = part_sums[kLongRows + r];
+      uint32_t bits = p0 + p1;
+      if (!raw) {
+        float f = ints ? static_cast<float>(static_cast<int>(bits))
+                       : __builtin_bit_cast(float, p0) + __builtin_bit_cast(float, p1);
+        if (!(g.mode & (kModeGrouped | kModeXscale))) f = sc * (BF16 ? 2.0f * f : f);
+        bits = __builtin_bit_cast(uint32_t, f);
+      }
+      put_y(bits, rout, 4u * static_cast<uint32_t>(range.first + r), 0, (g.mode & kModeAdd) != 0, raw);
+    }
+  }
 }
 
 using FastFn = void (*)(const KernelArgs);

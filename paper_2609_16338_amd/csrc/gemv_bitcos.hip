@@ -22,6 +22,7 @@ FastFn pick_fast_seg_8(int per_lane, bool bf16, bool table);
 FastFn pick_fast_seg_16(int per_lane, bool bf16, bool table);
 FastFn pick_fast_seg_32(int per_lane, bool bf16, bool table);
 FastFn pick_fast_seg_64(int per_lane, bool bf16, bool table);
+FastFn pick_fast_long(int per_lane, bool bf16);
 FastFn pick_diag_seg_4(int per_lane, bool bf16, bool table);
 FastFn pick_diag_seg_8(int per_lane, bool bf16, bool table);
 FastFn pick_diag_seg_16(int per_lane, bool bf16, bool table);
@@ -95,6 +96,32 @@ int launch_bitcos(const BatchHeader& h, const GemvDesc* table_dev, const GemvDes
   return bitcos_launch_status();
 }
 
+// One batch-1 GEMV of rows that two waves share: `per_lane` words per lane of
+// the two (0: the rows are longer than that holds).
+static int long_words(const GemvDesc& d, bool bf16) {
+  const int w = (d.upr + 127) / 128;
+  return w <= (bf16 ? kMaxWordsBf16 : kMaxWordsI8) ? w : 0;
+}
+static int launch_bitcos_long(const GemvDesc& d, int per_lane, bool bf16, void* stream) {
+  bitcos_k::FastFn fn = bitcos_k::pick_fast_long(per_lane, bf16);
+  if (!fn) return BITCOS_E_UNSUPPORTED;
+  bitcos_k::KernelArgs a;
+  a.table = nullptr;
+  a.total_units = d.n;  // a row per step
+  a.count = 1;
+  a.split = 1;
+  a.one = d;
+  a.one.units = d.n;
+  a.one.offset_stride = 1;
+  const int threads = bitcos_k::fast_threads(per_lane, bf16);
+  int64_t blocks = persistent_blocks(reinterpret_cast<const void*>(fn), d.n, threads);
+  if (blocks <= 0) return BITCOS_E_HIP;
+  const int64_t least = (static_cast<int64_t>(d.n) + bitcos_k::kLongRows - 1) / bitcos_k::kLongRows;
+  if (blocks < least) blocks = least;
+  hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(threads), 0, static_cast<hipStream_t>(stream), a);
+  return bitcos_launch_status();
+}
+
 }  // namespace bitcos
 
 extern "C" int bitcos_gemv(const bitcos_layout* L, const void* blob_dev, int32_t m,
@@ -109,6 +136,10 @@ extern "C" int bitcos_gemv(const bitcos_layout* L, const void* blob_dev, int32_t
     bitcos::GemvDesc d;
     int st = bitcos::make_desc(L, blob_dev, x_dev, xscale_dev, y_dev, x_dtype, y_mode, &d, m);
     if (st) return st;
+    if (m == 1) {
+      const bool bf16 = x_dtype == BITCOS_X_BF16;
+      if (const int w = bitcos::long_words(d, bf16)) return bitcos::launch_bitcos_long(d, w, bf16, stream);
+    }
     bitcos::BatchHeader h{};
     h.split = bitcos::mfma_split(bitcos::mfma_units(d), bitcos::mfma_steps(d));
     bitcos::to_mfma_units(&d, h.split);
