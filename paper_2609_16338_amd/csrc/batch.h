@@ -112,6 +112,8 @@ inline int gemv_rows(GemvEntry gemv, const bitcos_layout* L, const void* blob_de
 // small-batch kernel with one activation row, when it takes the layout.
 bool batch1_on_small_batch(const bitcos_layout* L, int32_t x_dtype);
 
+constexpr int kMfmaWgWaves = 8;  // waves of a workgroup
+
 // Units (of 32 rows) and steps of a unit (four 128-weight groups each) of a
 // descriptor in the small-batch kernel.
 inline int64_t mfma_units(const GemvDesc& d) { return (d.n + kMfmaUnitRows - 1) / kMfmaUnitRows; }
@@ -126,10 +128,9 @@ inline int32_t mfma_steps(const GemvDesc& d) { return (d.ngroups + 3) / 4; }
 // Kernel times whole -> split (us, bf16): 4096 x 4096 with 4 rows 23.0 -> 9.2,
 // 4096 x 12288 with 4 rows 59.7 -> 17.3 (8 parts), 5120 x 25600 with one row
 // 120 -> 31 (8 parts), 25600 x 5120 with 16 rows 33 -> 27 (2 parts).
-constexpr int kMfmaWaves = 2048;  // 256 CUs x 8 waves
 inline int32_t mfma_split(int64_t units, int32_t most_steps) {
   int32_t s = 1;
-  while (s < 8 && units * (2 * s) <= kMfmaWaves && 2 * s <= most_steps) s *= 2;
+  while (s < kMfmaWgWaves && units * (2 * s) <= 256 * kMfmaWgWaves && 2 * s <= most_steps) s *= 2;  // 256 CUs
   return s;
 }
 

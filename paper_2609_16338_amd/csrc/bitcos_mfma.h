@@ -70,18 +70,9 @@ constexpr int kMfmaRows = kMfmaTile * kMfmaRT;  // rows per work unit
 // registers (bf16).  int8 at 3 waves per SIMD and without the lookahead
 // spills with activation scales and measured slower.  Host and device both
 // use it.
-constexpr int mfma_threads(bool bf16, bool xs) {
-  (void)bf16;
-  (void)xs;
-  return 512;
-}
+constexpr int kMfmaThreads = 64 * bitcos::kMfmaWgWaves;
 constexpr int kMfmaMaxBatch = 16;
 constexpr int kSignStride = 21;  // LDS dwords per staged sign row (20 used; odd spreads banks)
-// The table lookups of group q + 1 are issued before group q's arithmetic.
-constexpr bool mfma_lookahead(bool bf16) {
-  (void)bf16;
-  return true;
-}
 // Activation loads: each load reads whole 16-byte pieces of a few batch
 // rows in order (fully used cache lines) and the wave's transpose buffer in
 // LDS hands every lane its MFMA operand.  Loading each lane's operand
@@ -90,11 +81,20 @@ constexpr bool mfma_lookahead(bool bf16) {
 // layers, us per step, bf16 / int8: 597 / 576 against 573 / 576 at M = 4,
 // 843 / 670 against 651 / 611 at M = 16).
 constexpr int mfma_xrow(bool bf16) { return (bf16 ? 256 : 128) + 16; }  // one group's activations of a batch row, padded
-constexpr int mfma_xbuf_bytes(bool bf16) { return 16 * mfma_xrow(bf16); }
+// ONE: the batch rows fit one 1 KB load per group (4 bf16 rows, 8 int8 rows),
+// so a lane keeps one piece of a group instead of four (bf16) or two, and as
+// many writes to the transpose buffer fall away: about 45 registers and a
+// tenth of the LDS's work at 4 bf16 rows.  us before -> after: 3-layer
+// Qwen3-32B-like set with 4 rows bf16 166 -> 143, int8 145 -> 138; at more rows
+// the kernel is as it was.  (12 waves per workgroup without the group
+// lookahead, which fit then too: 144 and 140, and 13.6 against 8.8 on a
+// 6144 x 4096 launch.)
+constexpr int mfma_one_rows(bool bf16) { return bf16 ? 4 : 8; }
+constexpr int mfma_xbuf_bytes(bool bf16, bool one) { return (one ? mfma_one_rows(bf16) : 16) * mfma_xrow(bf16); }
 // Sign-table copies (tables.h): 32 when the tables and the waves' sign
 // stages fit the LDS, else 16.
-constexpr int mfma_sign_copies(bool bf16) {
-  return 65536 + 2048 * 32 + (mfma_threads(bf16, false) / 64) * (kMfmaRows * kSignStride * 4 + mfma_xbuf_bytes(bf16)) <=
+constexpr int mfma_sign_copies(bool bf16, bool one) {
+  return 65536 + 2048 * 32 + bitcos::kMfmaWgWaves * (kMfmaRows * (kSignStride + 1) * 4 + mfma_xbuf_bytes(bf16, one)) <=
                  kLdsBytes
              ? 32
              : 16;
@@ -109,19 +109,20 @@ struct MStep {
   bool valid;
 };
 
-template <bool BF16, bool XS, bool TABLE, bool SPLIT>
-__global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(const KernelArgs a) {
-  constexpr int CT = mfma_sign_copies(BF16);
-  constexpr int THREADS = mfma_threads(BF16, XS);
+template <bool BF16, bool XS, bool TABLE, bool SPLIT, bool ONE>
+__global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelArgs a) {
+  constexpr int CT = mfma_sign_copies(BF16, ONE);
+  constexpr int THREADS = kMfmaThreads;
   constexpr int WPB = THREADS / kWave;
   constexpr int RT = kMfmaRT;
   constexpr int ELEM = BF16 ? 2 : 1;  // bytes per activation
   constexpr int NA = BF16 ? 4 : 2;    // MFMAs (16-byte activation pieces) per word
+  constexpr int NL = ONE ? 1 : NA;    // activation loads per group
   using CV = typename std::conditional<BF16, f32x4_t, i32x4_t>::type;
 
   __shared__ FastTables<BF16, CT> tab;
   __shared__ uint32_t sstage[WPB * kMfmaRows * kSignStride];
-  __shared__ uint4 xbufs[WPB * mfma_xbuf_bytes(BF16) / 16];
+  __shared__ uint4 xbufs[WPB * mfma_xbuf_bytes(BF16, ONE) / 16];
   __shared__ uint32_t part_nnz[SPLIT ? WPB * kMfmaRows : 1];  // split units: non-zeros of each row in each wave's part
   static_assert(sizeof(tab) + sizeof(sstage) + sizeof(xbufs) + sizeof(part_nnz) <= kLdsBytes, "small-batch kernel LDS");
 
@@ -135,8 +136,8 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
   const int total = static_cast<int>(a.total_units);
   const int nwaves = static_cast<int>(gridDim.x) * WPB;
   const int per = whole ? (total + nwaves - 1) / nwaves : 1;
-  const int part = whole ? 0 : wave & (split - 1);
-  const int S0 = whole ? per * wave : wave / split;
+  const int part = whole ? 0 : wv % split;  // `split` divides the workgroup's waves
+  const int S0 = whole ? per * wave : static_cast<int>(blockIdx.x) * (WPB / split) + wv / split;
   const int U1 = min(S0 + per, total);
   bool has = S0 < U1;
 
@@ -145,9 +146,11 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
   const uint32_t gm1 = lane_mask((g & 1) != 0), gm2 = lane_mask((g & 2) != 0);
   const FastLane fl = fast_lane<BF16, CT>(lane);
   uint32_t* const stage = sstage + wv * (kMfmaRows * kSignStride);
-  uint8_t* const xbuf = reinterpret_cast<uint8_t*>(xbufs) + wv * mfma_xbuf_bytes(BF16);
+  uint8_t* const xbuf = reinterpret_cast<uint8_t*>(xbufs) + wv * mfma_xbuf_bytes(BF16, ONE);
   constexpr int XROW = mfma_xrow(BF16);
   constexpr int XLR = BF16 ? 16 : 8;  // lanes per batch row in a coalesced load (16-byte pieces)
+  static_assert(mfma_one_rows(BF16) == 64 / XLR, "the rows of one load");
+  const int xrow = ONE ? nr & (64 / XLR - 1) : nr;  // the lane's batch row of A (ONE: rows past the load's repeat)
 
   // ---- fetch side: the GEMV whose step is being fetched; fbeg / fend: its
   // first step in the launch and one past its last, fC: steps per unit.
@@ -260,7 +263,7 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
   };
   // Activations of group q of a step: 32 of batch row nr at the lane's word
   // (and with XS, the activation scales of batch rows 4 g + i).
-  u32x4_t A[4][NA];
+  u32x4_t A[4][NL];
   // Activation scales of the step (XS): lane (nr, g) holds batch row
   // 4 g + nr % 4 at the step's four groups; a lane takes batch row 4 g + i's
   // from lane i of its quad.
@@ -276,7 +279,7 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
     // Loads whose batch rows are all past M are skipped: those rows' MFMA
     // results are never stored, so stale registers there are harmless.
 #pragma unroll
-    for (int jj = 0; jj < NA; ++jj) {
+    for (int jj = 0; jj < NL; ++jj) {
       const uint32_t so = (static_cast<uint32_t>((64 / XLR) * jj) * ukk + 128u * gi) * ELEM;
       if (jj == 0 || (64 / XLR) * jj < fM) A[q][jj] = ld128_s(rx, lx, __builtin_amdgcn_readfirstlane(ok ? so : kOOB));
     }
@@ -499,10 +502,9 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
       }
     };
     // Table lookups of a group: per tile, the lane's word and its 64-bit
-    // sign window from the staged block.  bf16 looks group 0 up here and, in
-    // group q, group q + 1 while q's weights are built and multiplied; int8
-    // looks each group up where it is used.  The two tiles' MFMA chains
-    // alternate so consecutive MFMAs do not depend on each other.
+    // sign window from the staged block: group 0 here and, in group q, group
+    // q + 1 while q's weights are built and multiplied.  The two tiles' MFMA
+    // chains alternate so consecutive MFMAs do not depend on each other.
     auto lookup1 = [&](int q, int r) {
       const uint32_t* srow = stage + (kMfmaTile * r + nr) * kSignStride;
       const uint32_t bpos = rel[r][q];
@@ -528,15 +530,12 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
                                                      __builtin_bit_cast(i32x4_t, w), c, 0, 0, 0);
       }
     };
-    constexpr bool LA = mfma_lookahead(BF16);
     Look<BF16> lk[2][RT];
-    if constexpr (LA) {
 #pragma unroll
-      for (int r = 0; r < RT; ++r) lk[0][r] = lookup1(0, r);
-    }
+    for (int r = 0; r < RT; ++r) lk[0][r] = lookup1(0, r);
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (LA && q + 1 < 4) {
+      if (q + 1 < 4) {
 #pragma unroll
         for (int r = 0; r < RT; ++r) lk[(q + 1) & 1][r] = lookup1(q + 1, r);
       }
@@ -544,26 +543,17 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
       // buffer: lane (nr, g) takes batch row nr at its word's pieces.
       u32x4_t Aq[NA];
 #pragma unroll
-      for (int jj = 0; jj < NA; ++jj)
+      for (int jj = 0; jj < NL; ++jj)
         *reinterpret_cast<u32x4_t*>(xbuf + ((64 / XLR) * jj + lane / XLR) * XROW + 16 * (lane % XLR)) = A[q][jj];
 #pragma unroll
-      for (int j = 0; j < NA; ++j) Aq[j] = *reinterpret_cast<const u32x4_t*>(xbuf + nr * XROW + 16 * (NA * g + j));
+      for (int j = 0; j < NA; ++j) Aq[j] = *reinterpret_cast<const u32x4_t*>(xbuf + xrow * XROW + 16 * (NA * g + j));
       CV c[RT];
 #pragma unroll
       for (int r = 0; r < RT; ++r) c[r] = CV{0, 0, 0, 0};
-      if constexpr (LA) {  // the two tiles' chains alternate
 #pragma unroll
-        for (int j = 0; j < NA; ++j)
+      for (int j = 0; j < NA; ++j)  // the two tiles' chains alternate
 #pragma unroll
-          for (int r = 0; r < RT; ++r) c[r] = mfma_word(lk[q & 1][r], Aq, j, c[r]);
-      } else {  // one tile's lookups live at a time
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-          const Look<BF16> L = lookup1(q, r);
-#pragma unroll
-          for (int j = 0; j < NA; ++j) c[r] = mfma_word(L, Aq, j, c[r]);
-        }
-      }
+        for (int r = 0; r < RT; ++r) c[r] = mfma_word(lk[q & 1][r], Aq, j, c[r]);
 #pragma unroll
       for (int r = 0; r < RT; ++r) cg[q & 1][r] = c[r];
       // This group's activations are consumed: fetch step t+1's.
@@ -595,12 +585,12 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
   }
   if constexpr (whole) return;
 
-  // Split units: every part's sums go to its wave's transpose buffer (8 of
-  // 64 lanes' values, 2 KB), and each of the unit's waves adds 8 / split of
+  // Split units: every part's sums go to its wave's sign stage (8 of 64
+  // lanes' values, 2 KB), and each of the unit's waves adds 8 / split of
   // them over the parts, in order, and stores.
-  static_assert(mfma_xbuf_bytes(BF16) >= RT * 4 * kWave * 4, "a wave's sums fit its transpose buffer");
-  uint32_t* const sums = reinterpret_cast<uint32_t*>(xbufs);
-  constexpr int kSumStride = mfma_xbuf_bytes(BF16) / 4;
+  uint32_t* const sums = sstage;
+  constexpr int kSumStride = kMfmaRows * kSignStride;
+  static_assert(kSumStride >= RT * 4 * kWave, "a wave's sums fit its sign stage");
   if (S0 < U1) decode_enter(fdi);
   const bool ints = !BF16 && !scaled;
 #pragma unroll
@@ -630,15 +620,17 @@ __global__ void __launch_bounds__(mfma_threads(BF16, XS)) bitcos_mfma_kernel(con
 
 using MfmaFn = void (*)(const KernelArgs);
 
-template <bool BF16, bool XS>
+template <bool BF16, bool XS, bool ONE>
 MfmaFn pick_mfma_t(bool table, bool split) {
-  if (split) return table ? bitcos_mfma_kernel<BF16, XS, true, true> : bitcos_mfma_kernel<BF16, XS, false, true>;
-  return table ? bitcos_mfma_kernel<BF16, XS, true, false> : bitcos_mfma_kernel<BF16, XS, false, false>;
+  if (split)
+    return table ? bitcos_mfma_kernel<BF16, XS, true, true, ONE> : bitcos_mfma_kernel<BF16, XS, false, true, ONE>;
+  return table ? bitcos_mfma_kernel<BF16, XS, true, false, ONE> : bitcos_mfma_kernel<BF16, XS, false, false, ONE>;
 }
 
-inline MfmaFn pick_mfma(bool bf16, bool xs, bool table, bool split) {
-  if (bf16) return xs ? pick_mfma_t<true, true>(table, split) : pick_mfma_t<true, false>(table, split);
-  return xs ? pick_mfma_t<false, true>(table, split) : pick_mfma_t<false, false>(table, split);
+template <bool BF16>
+MfmaFn pick_mfma(bool xs, bool table, bool split, bool one) {
+  if (one) return xs ? pick_mfma_t<BF16, true, true>(table, split) : pick_mfma_t<BF16, false, true>(table, split);
+  return xs ? pick_mfma_t<BF16, true, false>(table, split) : pick_mfma_t<BF16, false, false>(table, split);
 }
 
 }  // namespace bitcos_k

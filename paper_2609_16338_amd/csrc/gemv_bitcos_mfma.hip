@@ -18,14 +18,16 @@ int launch_bitcos_mfma(const BatchHeader& h, const GemvDesc* table_dev, const Ge
   if (h.m == 1 && !h.small_batch) return BITCOS_E_UNSUPPORTED;
   if (h.total_units < 1 || h.total_units >= (int64_t(1) << 31)) return BITCOS_E_UNSUPPORTED;
   const bool bf16 = h.x_dtype == BITCOS_X_BF16;
-  bitcos_k::MfmaFn fn = bitcos_k::pick_mfma(bf16, h.any_xscale != 0, table_dev != nullptr, h.split > 1);
+  const bool one_load = h.m <= bitcos_k::mfma_one_rows(bf16), xs = h.any_xscale != 0, table = table_dev != nullptr;
+  bitcos_k::MfmaFn fn = bf16 ? bitcos_k::pick_mfma<true>(xs, table, h.split > 1, one_load)
+                             : bitcos_k::pick_mfma<false>(xs, table, h.split > 1, one_load);
   bitcos_k::KernelArgs a;
   a.table = table_dev;
   a.total_units = h.total_units;
   a.count = h.count;
   a.split = h.split;
   a.one = one;
-  const int threads = bitcos_k::mfma_threads(bf16, h.any_xscale != 0);
+  constexpr int threads = bitcos_k::kMfmaThreads;
   // Split units: every part has its wave.  Whole ones: a persistent grid.
   const int64_t blocks = h.split > 1 ? (h.total_units * h.split * 64 + threads - 1) / threads
                                      : persistent_blocks(reinterpret_cast<const void*>(fn), h.total_units, threads);
