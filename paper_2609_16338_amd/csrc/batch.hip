@@ -145,10 +145,10 @@ static int build_small_batch(int32_t count, int32_t m, const bitcos_layout* layo
     units += mfma_units(descs[i]);
     most_steps = mfma_steps(descs[i]) > most_steps ? mfma_steps(descs[i]) : most_steps;
   }
-  h->split = mfma_split(units, most_steps);
+  mfma_plan(units, most_steps, h);
   units = 0;
   for (int32_t i = 0; i < count; ++i) {
-    to_mfma_units(&descs[i], h->split);
+    to_mfma_units(&descs[i], *h);
     descs[i].unit_begin = units;
     units += descs[i].units;
   }

@@ -13,7 +13,8 @@
 // so GEMVs of different K in one launch leave no wave with several times the
 // others' work.
 // A launch of few units (batch.h: mfma_split) gives each unit to 2, 4 or 8
-// waves of a workgroup instead, which split its steps: every wave counts the
+// waves of a workgroup instead (of one tile, 16 rows, where there are no more
+// than 128 of 32), which split its steps: every wave counts the
 // non-zeros of its part (one pass over the presence words, while the tables
 // are built) so that those after it know where their signs start, and the
 // parts' sums are added in order through LDS.
@@ -63,8 +64,7 @@
 namespace bitcos_k {
 
 constexpr int kMfmaTile = 16;                   // output rows per MFMA tile
-constexpr int kMfmaRT = 2;                      // tiles per work unit
-constexpr int kMfmaRows = kMfmaTile * kMfmaRT;  // rows per work unit
+constexpr int kMfmaMaxRT = 2;                   // tiles per work unit (RT): two, or one where a launch has few rows
 // Workgroup size: one workgroup per CU (the decode tables fill most of the
 // LDS), 2 waves per SIMD: the group lookahead below holds about 240
 // registers (bf16).  int8 at 3 waves per SIMD and without the lookahead
@@ -94,7 +94,7 @@ constexpr int mfma_xbuf_bytes(bool bf16, bool one) { return (one ? mfma_one_rows
 // Sign-table copies (tables.h): 32 when the tables and the waves' sign
 // stages fit the LDS, else 16.
 constexpr int mfma_sign_copies(bool bf16, bool one) {
-  return 65536 + 2048 * 32 + bitcos::kMfmaWgWaves * (kMfmaRows * (kSignStride + 1) * 4 + mfma_xbuf_bytes(bf16, one)) <=
+  return 65536 + 2048 * 32 + bitcos::kMfmaWgWaves * (kMfmaTile * kMfmaMaxRT * (kSignStride + 1) * 4 + mfma_xbuf_bytes(bf16, one)) <=
                  kLdsBytes
              ? 32
              : 16;
@@ -109,21 +109,21 @@ struct MStep {
   bool valid;
 };
 
-template <bool BF16, bool XS, bool TABLE, bool SPLIT, bool ONE>
+template <bool BF16, bool XS, bool TABLE, bool SPLIT, bool ONE, int RT>
 __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelArgs a) {
   constexpr int CT = mfma_sign_copies(BF16, ONE);
   constexpr int THREADS = kMfmaThreads;
   constexpr int WPB = THREADS / kWave;
-  constexpr int RT = kMfmaRT;
+  constexpr int kRows = kMfmaTile * RT;  // rows per work unit
   constexpr int ELEM = BF16 ? 2 : 1;  // bytes per activation
   constexpr int NA = BF16 ? 4 : 2;    // MFMAs (16-byte activation pieces) per word
   constexpr int NL = ONE ? 1 : NA;    // activation loads per group
   using CV = typename std::conditional<BF16, f32x4_t, i32x4_t>::type;
 
   __shared__ FastTables<BF16, CT> tab;
-  __shared__ uint32_t sstage[WPB * kMfmaRows * kSignStride];
+  __shared__ uint32_t sstage[WPB * kRows * kSignStride];
   __shared__ uint4 xbufs[WPB * mfma_xbuf_bytes(BF16, ONE) / 16];
-  __shared__ uint32_t part_nnz[SPLIT ? WPB * kMfmaRows : 1];  // split units: non-zeros of each row in each wave's part
+  __shared__ uint32_t part_nnz[SPLIT ? WPB * kRows : 1];  // split units: non-zeros of each row in each wave's part
   static_assert(sizeof(tab) + sizeof(sstage) + sizeof(xbufs) + sizeof(part_nnz) <= kLdsBytes, "small-batch kernel LDS");
 
   const int lane = threadIdx.x & 63;
@@ -145,7 +145,7 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
   const int g = lane >> 4;
   const uint32_t gm1 = lane_mask((g & 1) != 0), gm2 = lane_mask((g & 2) != 0);
   const FastLane fl = fast_lane<BF16, CT>(lane);
-  uint32_t* const stage = sstage + wv * (kMfmaRows * kSignStride);
+  uint32_t* const stage = sstage + wv * (kRows * kSignStride);
   uint8_t* const xbuf = reinterpret_cast<uint8_t*>(xbufs) + wv * mfma_xbuf_bytes(BF16, ONE);
   constexpr int XROW = mfma_xrow(BF16);
   constexpr int XLR = BF16 ? 16 : 8;  // lanes per batch row in a coalesced load (16-byte pieces)
@@ -192,7 +192,7 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
   auto next_unit_offsets = [&](int u, uint32_t (&o)[RT]) {
     const int start = fbeg + (u + 1) * fC;
     const bool same = start < fend;
-    load_offsets(same ? fdi : min(fdi + 1, a.count - 1), same ? (u + 1) * kMfmaRows : 0, start < U1, o);
+    load_offsets(same ? fdi : min(fdi + 1, a.count - 1), same ? (u + 1) * kRows : 0, start < U1, o);
   };
 
   // First unit: the first one of the launch to start at or after S0; and the
@@ -230,7 +230,7 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
   // soffset kOOB.
   auto issue = [&](const MStep& s, Slot& d) {
     const uint32_t c = static_cast<uint32_t>(s.valid ? s.c : 0);
-    const uint32_t row0 = static_cast<uint32_t>(s.unit * kMfmaRows);
+    const uint32_t row0 = static_cast<uint32_t>(s.unit * kRows);
     // Presence: lane (nr, g) reads group g of the step (its four words, 16
     // bytes); place() transposes the four lanes' groups so that each lane
     // holds its word g of every group.
@@ -358,12 +358,12 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
   fs.valid = has;
   Slot cur, nxt;
   uint32_t offn[RT];
-  load_offsets(fdi, u0 * kMfmaRows, has, cur.pos);
+  load_offsets(fdi, u0 * kRows, has, cur.pos);
   if constexpr (SPLIT) {
 #pragma unroll
     for (int r = 0; r < RT; ++r) offn[r] = 0;
   }
-  uint32_t nnz[RT] = {0, 0};
+  uint32_t nnz[RT] = {};
   if (SPLIT && has) {
     // The lane's group of each of the part's steps, four steps' loads at a time.
     constexpr int kAtOnce = 4;
@@ -375,7 +375,7 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
           const bool in = c + t < c1 && 4 * (c + t) + g < fG;
-          const uint32_t sp = (static_cast<uint32_t>(u0 * kMfmaRows + kMfmaTile * r) * static_cast<uint32_t>(fupr) +
+          const uint32_t sp = (static_cast<uint32_t>(u0 * kRows + kMfmaTile * r) * static_cast<uint32_t>(fupr) +
                                16u * static_cast<uint32_t>(c + t)) * 4u;
           v[t][r] = ld128_s(rb, in ? lp : kOOB, __builtin_amdgcn_readfirstlane(c + t < c1 ? sp : 0u));
         }
@@ -395,13 +395,13 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
   build_fast_tables<BF16, CT, THREADS>(tab, threadIdx.x);
   if (SPLIT && g == 0) {
 #pragma unroll
-    for (int r = 0; r < RT; ++r) part_nnz[wv * kMfmaRows + kMfmaTile * r + nr] = nnz[r];
+    for (int r = 0; r < RT; ++r) part_nnz[wv * kRows + kMfmaTile * r + nr] = nnz[r];
   }
   __syncthreads();
   if (whole && !has) return;
   for (int p = 0; SPLIT && p < part; ++p) {
 #pragma unroll
-    for (int r = 0; r < RT; ++r) cur.pos[r] += part_nnz[(wv - part + p) * kMfmaRows + kMfmaTile * r + nr];
+    for (int r = 0; r < RT; ++r) cur.pos[r] += part_nnz[(wv - part + p) * kRows + kMfmaTile * r + nr];
   }
   issue(fs, cur);
   if constexpr (!SPLIT) next_unit_offsets(u0, offn);
@@ -565,7 +565,7 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
     __builtin_amdgcn_wave_barrier();
 
     if (whole && cs.last) {  // store the unit: y[m][row]; rows past n and batch rows past M are dropped
-      const int row0 = cs.unit * kMfmaRows;
+      const int row0 = cs.unit * kRows;
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         const int row = row0 + kMfmaTile * r + nr;
@@ -589,7 +589,7 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
   // lanes' values, 2 KB), and each of the unit's waves adds 8 / split of
   // them over the parts, in order, and stores.
   uint32_t* const sums = sstage;
-  constexpr int kSumStride = kMfmaRows * kSignStride;
+  constexpr int kSumStride = kRows * kSignStride;
   static_assert(kSumStride >= RT * 4 * kWave, "a wave's sums fit its sign stage");
   if (S0 < U1) decode_enter(fdi);
   const bool ints = !BF16 && !scaled;
@@ -612,7 +612,7 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
       else
         f += __builtin_bit_cast(float, w);
     }
-    const int row = u0 * kMfmaRows + kMfmaTile * (v >> 2) + nr;
+    const int row = u0 * kRows + kMfmaTile * (v >> 2) + nr;
     const uint32_t off = row < dn ? (static_cast<uint32_t>((4 * g + (v & 3)) * dn) + row) * 4u : kOOB;
     put_y(finish(f, n), ry, off, 0, dadd, raw);
   }
@@ -621,16 +621,21 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
 using MfmaFn = void (*)(const KernelArgs);
 
 template <bool BF16, bool XS, bool ONE>
-MfmaFn pick_mfma_t(bool table, bool split) {
+MfmaFn pick_mfma_t(bool table, bool split, int unit_rows) {
+  if (unit_rows == kMfmaTile)  // split units only
+    return table ? bitcos_mfma_kernel<BF16, XS, true, true, ONE, 1> : bitcos_mfma_kernel<BF16, XS, false, true, ONE, 1>;
   if (split)
-    return table ? bitcos_mfma_kernel<BF16, XS, true, true, ONE> : bitcos_mfma_kernel<BF16, XS, false, true, ONE>;
-  return table ? bitcos_mfma_kernel<BF16, XS, true, false, ONE> : bitcos_mfma_kernel<BF16, XS, false, false, ONE>;
+    return table ? bitcos_mfma_kernel<BF16, XS, true, true, ONE, 2> : bitcos_mfma_kernel<BF16, XS, false, true, ONE, 2>;
+  return table ? bitcos_mfma_kernel<BF16, XS, true, false, ONE, 2> : bitcos_mfma_kernel<BF16, XS, false, false, ONE, 2>;
 }
 
 template <bool BF16>
-MfmaFn pick_mfma(bool xs, bool table, bool split, bool one) {
-  if (one) return xs ? pick_mfma_t<BF16, true, true>(table, split) : pick_mfma_t<BF16, false, true>(table, split);
-  return xs ? pick_mfma_t<BF16, true, false>(table, split) : pick_mfma_t<BF16, false, false>(table, split);
+MfmaFn pick_mfma(bool xs, bool table, bool split, int unit_rows, bool one) {
+  if (one)
+    return xs ? pick_mfma_t<BF16, true, true>(table, split, unit_rows)
+              : pick_mfma_t<BF16, false, true>(table, split, unit_rows);
+  return xs ? pick_mfma_t<BF16, true, false>(table, split, unit_rows)
+            : pick_mfma_t<BF16, false, false>(table, split, unit_rows);
 }
 
 }  // namespace bitcos_k

@@ -141,8 +141,8 @@ extern "C" int bitcos_gemv(const bitcos_layout* L, const void* blob_dev, int32_t
       if (const int w = bitcos::long_words(d, bf16)) return bitcos::launch_bitcos_long(d, w, bf16, stream);
     }
     bitcos::BatchHeader h{};
-    h.split = bitcos::mfma_split(bitcos::mfma_units(d), bitcos::mfma_steps(d));
-    bitcos::to_mfma_units(&d, h.split);
+    bitcos::mfma_plan(bitcos::mfma_units(d), bitcos::mfma_steps(d), &h);
+    bitcos::to_mfma_units(&d, h);
     h.magic = bitcos::kBatchMagic;
     h.version = BITCOS_LAYOUT_VERSION;
     h.format = BITCOS_FMT_BITCOS;

@@ -8,7 +8,7 @@
 #include "bitcos_mfma.h"
 #include "launch_common.h"
 
-static_assert(bitcos_k::kMfmaRows == bitcos::kMfmaUnitRows, "host and kernel agree on the unit");
+static_assert(bitcos_k::kMfmaTile * bitcos_k::kMfmaMaxRT == bitcos::kMfmaUnitRows, "host and kernel agree on the unit");
 static_assert(bitcos_k::kMfmaMaxBatch == BITCOS_MAX_M, "one MFMA tile holds every activation row");
 
 namespace bitcos {
@@ -19,8 +19,8 @@ int launch_bitcos_mfma(const BatchHeader& h, const GemvDesc* table_dev, const Ge
   if (h.total_units < 1 || h.total_units >= (int64_t(1) << 31)) return BITCOS_E_UNSUPPORTED;
   const bool bf16 = h.x_dtype == BITCOS_X_BF16;
   const bool one_load = h.m <= bitcos_k::mfma_one_rows(bf16), xs = h.any_xscale != 0, table = table_dev != nullptr;
-  bitcos_k::MfmaFn fn = bf16 ? bitcos_k::pick_mfma<true>(xs, table, h.split > 1, one_load)
-                             : bitcos_k::pick_mfma<false>(xs, table, h.split > 1, one_load);
+  bitcos_k::MfmaFn fn = bf16 ? bitcos_k::pick_mfma<true>(xs, table, h.split > 1, h.mfma_rows, one_load)
+                             : bitcos_k::pick_mfma<false>(xs, table, h.split > 1, h.mfma_rows, one_load);
   bitcos_k::KernelArgs a;
   a.table = table_dev;
   a.total_units = h.total_units;

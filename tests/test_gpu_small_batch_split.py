@@ -26,10 +26,12 @@ def _need_gpu():
 
 
 # (n, k, m): 32-row units x parts against 2048 waves, steps of 512 weights.
-# 8 parts up to n = 8192, 4 up to 16384, 2 up to 32768, then whole units; no
+# 8 parts up to n = 8192 (of 16-row units up to 4096, where k has 8 steps), 4 up
+# to 16384, 2 up to 32768, then whole units; no
 # more parts than steps (k = 384: one step, 1024: two, 2560: five).
 SHAPES = [(1, 128, 2), (33, 384, 3), (45, 1024, 16), (40, 2560, 5), (70, 4096, 4), (8192, 4224, 2), (50, 2560, 8), (8193, 4224, 7),
-          (16384, 2176, 2), (16385, 2176, 9), (32768, 1152, 2), (32769, 1152, 3), (64, 25600, 1), (37, 33024, 1)]
+          (16384, 2176, 2), (16385, 2176, 9), (32768, 1152, 2), (32769, 1152, 3), (64, 25600, 1),
+          (37, 33024, 1), (4096, 4096, 3), (4097, 4096, 2), (2000, 4224, 16), (17, 4096, 6)]
 
 
 def _rows(n):
