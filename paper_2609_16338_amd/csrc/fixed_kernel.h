@@ -280,8 +280,12 @@ __device__ __forceinline__ uint32_t code_byte(const uint32_t (&A)[NA], int i) {
 // Pieces of 16 bytes that the workgroup's first activations pass through LDS at once.
 constexpr int kXRoom = 512;
 
+// Seven waves per SIMD for the one-block int8 tile, whose registers just allow
+// it (96 x 8192 x 4096: 165 us, 171 at six).
+constexpr int trit5_waves(bool bf16, int bk) { return !bf16 && bk == 1 ? 7 : 1; }
+
 template <int BK, int SEG, bool BF16, bool TABLE>
-__global__ void __launch_bounds__(fixed_threads(false, BF16, BK)) trit5_gemv_kernel(const KernelArgs a) {
+__global__ void __launch_bounds__(fixed_threads(false, BF16, BK), trit5_waves(BF16, BK)) trit5_gemv_kernel(const KernelArgs a) {
   using Tables = typename std::conditional<BF16, Trit5TablesBf16, Trit5TablesI8>::type;
   constexpr int NT = fixed_threads(false, BF16, BK);
   constexpr int WPB = NT / kWave;
@@ -447,7 +451,10 @@ __global__ void __launch_bounds__(fixed_threads(false, BF16, BK)) trit5_gemv_ker
 // l reads copy l % kBit2Copies): a ds_read_b64 serves 32 lanes at a time;
 // 16 copies (32 KB) leave room for four 256-thread workgroups per CU, which
 // measured faster than 32 conflict-free copies with one 512-thread
-// workgroup.
+// workgroup.  Beside the kernel's 8 KB of passing activations it is four and
+// not five: five times 32 KB is all of the LDS, five workgroups are counted
+// into the grid, and the fifth ran after the others (96 x 8192 x 4096: 364 us
+// against 263, 2.7 TB/s of blob; three workgroups 318, two 442).
 constexpr int kBit2Copies = 16;
 struct Bit2TablesBf16 {
   uint2 t[256 * kBit2Copies];
@@ -470,10 +477,9 @@ template <int WB, int SEG, bool BF16, bool TABLE>
 __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kernel(const KernelArgs a) {
   constexpr int NT = fixed_threads(true, BF16, WB);
   constexpr int WPB = NT / kWave;
-  struct alignas(16) XBuf {
-    piece_t v[kXRoom];
-  };
-  __shared__ alignas(16) typename std::conditional<BF16, Bit2TablesBf16, XBuf>::type tab;
+  __shared__ typename std::conditional<BF16, Bit2TablesBf16, char>::type tab;
+  __shared__ piece_t xbuf[kXRoom];
+
   constexpr int R = kWave / SEG;
   constexpr int NX = BF16 ? 8 : 4;  // activation dwords per 16-weight word
   using Acc = typename std::conditional<BF16, float, int>::type;
@@ -566,9 +572,7 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
     arrange_x();
   };
 
-  // As in the five-trit kernel; the bf16 variant's activations pass through
-  // the memory of its table, which is built after them (four workgroups of
-  // 40 KB would fill the LDS to the last byte).
+  // As in the five-trit kernel.
   Step s1 = gen.next(a);
   uint32_t cw1[WB];
   uint16_t SC1[NQ];
@@ -580,7 +584,7 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
   }
   const bool shared = !s1.valid || same_x<TABLE>(a, s1.di, fdi);
   if (s1.valid && shared) enter_x(s1.di);
-  fx.share(reinterpret_cast<piece_t*>(&tab), threadIdx.x, j, shared && s1.valid, xr);
+  fx.share(xbuf, threadIdx.x, j, shared && s1.valid, xr);
   arrange_x();
   if constexpr (BF16) {
     build_bit2_bf16(tab, threadIdx.x, NT);
