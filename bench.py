@@ -124,7 +124,7 @@ def emit(obj, args):
 _COMMON_SOURCES = ["bitcos_kernel.h", "tables.h", "device_common.h", "batch.h", "batch.hip", "launch_common.h",
                    "plan.h", "start.h"]
 KERNEL_SOURCES = {
-    "bitcos_fast_kernel": ["bitcos_fast.h", "gemv_bitcos.hip"] + _COMMON_SOURCES,
+    "bitcos_fast_kernel": ["bitcos_fast.h", "mfma_common.h", "gemv_bitcos.hip"] + _COMMON_SOURCES,
     "bitcos_diag_kernel": ["bitcos_diag.h", "bitcos_fast.h", "mfma_common.h", "gemv_bitcos.hip"] + _COMMON_SOURCES,
     "bitcos_mfma_kernel": ["bitcos_mfma.h", "mfma_common.h", "gemv_bitcos_mfma.hip"] + _COMMON_SOURCES,
     "trit5_gemv_kernel": ["fixed_kernel.h", "fixed_trit5.hip", "gemv_fixed.hip"] + _COMMON_SOURCES,
@@ -199,7 +199,7 @@ def stored_traffic(workload, launch):
 
 
 def launch_label(top, m):
-    """Kernel, tile and GEMV count of a batched launch (bf16 activations)."""
+    """Kernel, tile, GEMV count and activation rows of a batched launch (bf16 activations)."""
     from paper_2609_16338_amd import _native as N
     from paper_2609_16338_amd import api
 
@@ -207,7 +207,8 @@ def launch_label(top, m):
     kname = {N.KERNEL_MATRIX: "bitcos_diag_kernel", N.KERNEL_STREAMING: "bitcos_fast_kernel",
              N.KERNEL_GENERAL: "bitcos_gemv_kernel", N.KERNEL_SMALL_BATCH: "bitcos_mfma_kernel",
              }.get(kinds.pop(), "?") if len(kinds) == 1 else "mixed"
-    return f"{kname}<{top.tile[0]},{top.tile[1]},bf16,table>: {len(top.entries)} GEMVs in one launch"
+    rows = f", {m} activation rows" if m > 1 else ""  # another M is another launch: its own traffic and counters
+    return f"{kname}<{top.tile[0]},{top.tile[1]},bf16,table>: {len(top.entries)} GEMVs in one launch{rows}"
 
 
 # ---------------------------------------------------------------------------
