@@ -280,8 +280,8 @@ __device__ __forceinline__ uint32_t code_byte(const uint32_t (&A)[NA], int i) {
 // Pieces of 16 bytes that the workgroup's first activations pass through LDS at once.
 constexpr int kXRoom = 512;
 
-// Seven waves per SIMD for the one-block int8 tile, whose registers just allow
-// it (96 x 8192 x 4096: 165 us, 171 at six).
+// Seven waves per SIMD for the one-block int8 tile: 73 registers, cut to 72 with
+// two to six dwords spilled (96 x 8192 x 4096: 165 us, 171 at six waves).
 constexpr int trit5_waves(bool bf16, int bk) { return !bf16 && bk == 1 ? 7 : 1; }
 
 template <int BK, int SEG, bool BF16, bool TABLE>
