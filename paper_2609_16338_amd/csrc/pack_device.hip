@@ -199,8 +199,10 @@ __device__ __forceinline__ Sections sections(const PackTarget& p, const void* ws
   return s;
 }
 
-// Unit offsets, scales, zero padding, and zeros in the sign dwords that hold
-// a row's first bit (which rows may share).
+// Unit offsets, scales, zero padding, and zeros in the sign dwords that no row
+// has to itself: those that hold a row's first bit (which rows may share), and
+// those past the last planned row where the layout has room for more signs (a
+// layout of more non-zeros than the workspace's plan).
 constexpr int kSideThreads = 256;
 __global__ void __launch_bounds__(kSideThreads) pack_side_kernel(const uint16_t* scales, PackTarget p, void* ws) {
   const Sections s = sections(p, ws);
@@ -215,6 +217,8 @@ __global__ void __launch_bounds__(kSideThreads) pack_side_kernel(const uint16_t*
     const uint32_t at = rows[i];
     if (at <= s.nnz) signs[at >> 5] = 0;
   }
+  const uint64_t sign_dwords = (s.nnz + 31) / 32;
+  for (uint64_t d = (static_cast<uint64_t>(rows[p.n]) + 31) / 32 + t; d < sign_dwords; d += stride) signs[d] = 0;
   for (int64_t u = t; u <= p.units; u += stride)
     offsets[u] = rows[u * p.unit_rows < p.n ? u * p.unit_rows : p.n];
   bool bad = false;

@@ -155,3 +155,40 @@ def test_device_pack_argument_errors():
     wd = torch.zeros((64, 128), dtype=torch.int8, device="cuda")
     assert lib.bitcos_plan_device(ctypes.c_void_p(wd.data_ptr()), 64, 128, 128, 0, ctypes.c_void_p(ws.data_ptr()),
                                   16, ctypes.byref(L), None) == N.E_SPACE
+
+
+def test_device_pack_layout_of_more_nonzeros_than_the_plan():
+    """A layout kept from a plan with more non-zeros than the workspace's latest
+    plan: the sign stream past the planned signs is zeros, whatever the
+    destination held."""
+    lib = N.lib()
+    import ctypes
+    n, k = 40, 1024
+    w = wl.ternary(n, k, 0.3, wl.rng_for(81))
+    fewer = w.copy()
+    fewer[n // 2:] = 0  # about half of the signs: whole dwords of the longer stream are left over
+    sc = wl.fp16_uniform((n * k // 128,), 0.01, 0.1, wl.rng_for(82))
+    sd = torch.from_numpy(sc.view(np.int16)).cuda()
+    ws_bytes = lib.bitcos_plan_device_workspace(n)
+    ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
+    dev = [torch.from_numpy(v).cuda() for v in (w, fewer)]
+    layouts = []
+    for wd in dev:
+        L = N.Layout()
+        N.check(lib.bitcos_plan_device(wd.data_ptr(), n, k, 128, 0, ws.data_ptr(), ws_bytes, ctypes.byref(L), None),
+                "plan")
+        layouts.append(L)
+    L, short = layouts
+    assert short.nnz + 64 < L.nnz
+    # The reference: the smaller matrix's own sections at the larger layout's places, zeros between them.
+    _, own = api.plan_and_pack(N.FMT_BITCOS, fewer, sc, 128)
+    want = np.zeros(L.total_bytes, dtype=np.uint8)
+    for sec in range(4):
+        src, size = short.sec_off[sec], short.sec_bytes[sec]
+        want[L.sec_off[sec]:L.sec_off[sec] + size] = own[src:src + size]
+    for fill in (0x00, 0xFF):
+        say("pack_device, layout of more non-zeros", hex(fill))
+        dst = torch.full((L.total_bytes,), fill, dtype=torch.uint8, device="cuda")
+        N.check(lib.bitcos_pack_device(dev[1].data_ptr(), sd.data_ptr(), ctypes.byref(L), ws.data_ptr(), ws_bytes,
+                                       dst.data_ptr(), L.total_bytes, None), "pack")
+        assert np.array_equal(dst.cpu().numpy(), want)
