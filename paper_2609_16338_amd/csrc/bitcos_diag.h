@@ -276,7 +276,7 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
     const FastStep& s = st[k];
     if (s.valid && s.di != idi) fetch_enter(s.di);
     const uint32_t unit = static_cast<uint32_t>(s.row0 / R);
-    const uint32_t soff_p = __builtin_amdgcn_readfirstlane(s.valid ? unit * row_bytes : kOOB);
+    const uint32_t soff_p = unit * row_bytes | s.oob;  // as in the streaming kernel
     // The lane's words: the first four in one 16-byte load (dword-aligned;
     // dwords past the section read zero), the rest one by one.
     if constexpr (W >= 4) {

@@ -70,6 +70,7 @@ struct FastStep {
   int row0;       // first row
   uint32_t off0;  // first sign bit of the step
   uint32_t off1;  // first sign bit of the next step
+  uint32_t oob;   // kOOB past the wave's last step, else 0: part of every load's soffset
   bool valid;
 };
 
@@ -96,6 +97,7 @@ struct FastGen {
   __device__ __forceinline__ FastStep next(const KernelArgs& a) {
     FastStep s;
     s.valid = U < Uend;
+    s.oob = s.valid ? 0u : kOOB;
     s.di = di;
     s.row0 = 0;
     s.off0 = 0;
@@ -203,7 +205,7 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   int idi = -1;
   rsrc_t rb = make_rsrc(nullptr, 0), rg = rb, rs = rb;
   uint32_t row_bytes = 0, row_scale_bytes = 0;
-  bool grouped = false;
+  uint32_t no_scales = kOOB;  // kOOB without group scales
   uint32_t voff_p = 0;
   uint32_t voff_q[NQ];
 #pragma unroll
@@ -218,7 +220,7 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     rs = make_rsrc(g.scales, g.scales_bytes);
     row_bytes = static_cast<uint32_t>(g.upr) * 4u * R;
     row_scale_bytes = static_cast<uint32_t>(g.ngroups) * 2u * R;
-    grouped = (g.mode & kModeGrouped) != 0;
+    no_scales = (g.mode & kModeGrouped) ? 0u : kOOB;
     voff_p = (__umul24(static_cast<uint32_t>(rho), static_cast<uint32_t>(g.upr)) + static_cast<uint32_t>(w0)) * 4u;
     const int glast = max(g.ngroups - 1, 0);
 #pragma unroll
@@ -232,10 +234,14 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     const FastStep& s = st[k];
     if (s.valid && s.di != idi) fetch_enter(s.di);
     const uint32_t unit = static_cast<uint32_t>(s.row0 / R);
-    const uint32_t soff_p = __builtin_amdgcn_readfirstlane(s.valid ? unit * row_bytes : kOOB);
+    // Past the last step `unit` is 0 and oob all there is.  A choice between
+    // the two (s.valid ? ... : kOOB) goes through a lane mask, and takes the
+    // products with it: two quarter-rate vector multiplies a step (5 bf16 words
+    // on 32-lane rows: 5 of 316 vector instructions a step).
+    const uint32_t soff_p = unit * row_bytes | s.oob;
 #pragma unroll
     for (int w = 0; w < W; ++w) P[k][w] = __builtin_amdgcn_raw_buffer_load_b32(rb, voff_p + 4u * w, soff_p, 0);
-    const uint32_t soff_q = __builtin_amdgcn_readfirstlane((s.valid && grouped) ? unit * row_scale_bytes : kOOB);
+    const uint32_t soff_q = unit * row_scale_bytes | s.oob | no_scales;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) SC[k][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, voff_q[q], soff_q, 0);
   };

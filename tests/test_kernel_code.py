@@ -1,0 +1,36 @@
+"""What the compiler made of the kernels: properties of the device code that the
+kernels' speed rests on and that a small change of the source can lose."""
+
+import re
+
+import pytest
+
+import code_objects
+
+
+def _vector_products_read_back(body):
+    """v_readfirstlane of a value that a vector multiply (or a choice of one) made shortly before."""
+    found = []
+    made = {}  # VGPR -> index of the instruction that made it a product
+    for i, line in enumerate(body):
+        op, _, args = line.partition(" ")
+        regs = [r.strip() for r in args.split(",")]
+        if op == "v_readfirstlane_b32":
+            if i - made.get(regs[1], -99) < 16:
+                found.append(line)
+        elif op.startswith("v_") and regs:
+            if op == "v_mul_lo_u32" or any(i - made.get(r, -99) < 16 for r in regs[1:]):
+                made[regs[0]] = i
+            else:
+                made.pop(regs[0], None)
+    return found
+
+
+@pytest.mark.parametrize("seg", [4, 8, 16, 32, 64])
+def test_streaming_step_offsets_are_scalar(seg):
+    """A step's row offsets are products of uniform values: scalar multiplies, not vector
+    ones (quarter rate) whose result is read back into a scalar register."""
+    bodies = code_objects.disassembly(rf"bitcos_(fast|diag)_kernel<\d+, {seg}, ")
+    assert len(bodies) >= 2 * (16 + 8) * 2
+    bad = {name: found for name, body in bodies.items() if (found := _vector_products_read_back(body))}
+    assert not bad, f"{len(bad)} of {len(bodies)} kernels, e.g. {next(iter(bad.items()))}"
