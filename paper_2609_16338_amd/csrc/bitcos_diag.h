@@ -271,24 +271,25 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
     voff_p = (__umul24(static_cast<uint32_t>(rho), static_cast<uint32_t>(g.upr)) + static_cast<uint32_t>(w0)) * 4u;
   };
 
+  if constexpr (!TABLE) fetch_enter(0);
+
   auto issue = [&](auto stage_c) {
     constexpr int k = decltype(stage_c)::value;
     const FastStep& s = st[k];
-    if (s.valid && s.di != idi) fetch_enter(s.di);
+    if (TABLE && s.valid && s.di != idi) fetch_enter(s.di);
     const uint32_t unit = static_cast<uint32_t>(s.row0 / R);
     const uint32_t soff_p = unit * row_bytes | s.oob;  // as in the streaming kernel
-    // The lane's words: the first four in one 16-byte load (dword-aligned;
-    // dwords past the section read zero), the rest one by one.
-    if constexpr (W >= 4) {
-      const u32x4_t v = ld128_s(rb, voff_p, soff_p);
+    // Four words a load, as in the streaming kernel.
+    constexpr int kQuads = W / 4;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) P[k][w] = v[w];
+    for (int c = 0; c < kQuads; ++c) {
+      const u32x4_t v = ld128_s(rb, voff_p + 16u * c, soff_p);
 #pragma unroll
-      for (int w = 4; w < W; ++w) P[k][w] = __builtin_amdgcn_raw_buffer_load_b32(rb, voff_p + 4u * w, soff_p, 0);
-    } else {
-#pragma unroll
-      for (int w = 0; w < W; ++w) P[k][w] = __builtin_amdgcn_raw_buffer_load_b32(rb, voff_p + 4u * w, soff_p, 0);
+      for (int w = 0; w < 4; ++w) P[k][4 * c + w] = v[w];
     }
+#pragma unroll
+    for (int w = 4 * kQuads; w < W; ++w)
+      P[k][w] = __builtin_amdgcn_raw_buffer_load_b32(rb, voff_p + 4u * w, soff_p, 0);
     if constexpr (kRowOffsets) {  // rows past the matrix end read the last entry (nnz)
       const int e = min(static_cast<int>(unit) * gen.stride + rho, gen.last);
       ROFF[k] = ld32(ro, s.valid ? static_cast<uint32_t>(e) * 4u : kOOB);
@@ -336,9 +337,8 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
     ry = make_rsrc(g.y, g.y_bytes);
   };
 
-  // GEMV d's activations by the wave itself, 16 bytes a load (dword loads,
-  // which the compiler made of it without the table, took 15 us of a 27 us
-  // launch at 8 int8 words a lane); words past the row's end read zero.
+  // Table: GEMV d's activations by the wave itself, where it enters a GEMV
+  // with others than its workgroup's first; words past the row's end read zero.
   auto load_x = [&](int d) {
     const auto& g = desc_at<TABLE>(a, d);
     const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
@@ -379,13 +379,15 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
     const FastStep& s = st[k];
     wait_vmem_all();
     flush_store();
-    // Entering another GEMV: its activations, loaded and waited for before
+    // Table: entering another GEMV.  Its activations, loaded and waited for before
     // the next step's loads are issued, so that no wait inside the step
     // covers those loads.
-    if (s.di != xdi) {
-      enter_x(s.di);
-      load_x(s.di);
-      wait_vmem_all();
+    if constexpr (TABLE) {
+      if (s.di != xdi) {
+        enter_x(s.di);
+        load_x(s.di);
+        wait_vmem_all();
+      }
     }
     next();
     // LDS byte address of the stage buffer, in bits (cursors below count from
@@ -394,9 +396,11 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
     const uint32_t stage_bits =
         static_cast<uint32_t>(reinterpret_cast<size_t>((LdsU32*)stage_buf(stage_c))) * 8u + wave_bits;
     if (ragged) {
+      int nw = nwl;
+      if constexpr (W > 8) asm volatile("" : "+v"(nw));  // the words' masks, held across the loop, would be spilled
 #pragma unroll
       for (int w = 0; w < W; ++w)
-        if (w >= nwl) P[k][w] = 0u;
+        if (w >= nw) P[k][w] = 0u;
     }
     const uint32_t (&Pw)[W] = P[k];
     int pc[W];
@@ -495,9 +499,11 @@ __global__ void __launch_bounds__(diag_threads(W, BF16)) bitcos_diag_kernel(cons
   build_fast_tables<BF16, CT, NT>(tab, threadIdx.x);
   issue_signs(std::integral_constant<int, 0>{});
   bool shared = true;
-  if (st[0].valid) {
+  if constexpr (!TABLE) {
+    enter_x(0);
+  } else if (st[0].valid) {
     enter_x(st[0].di);
-    if constexpr (TABLE) {
+    {
       const auto &g = desc_at<TABLE>(a, st[0].di), &f = desc_at<TABLE>(a, fdi);
       shared = g.x == f.x && g.x_bytes == f.x_bytes;
     }

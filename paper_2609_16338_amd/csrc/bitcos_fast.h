@@ -200,7 +200,10 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   uint16_t SC[D][NQ];
 
   // Fetch side: buffer resources and lane offsets of the GEMV being fetched.
-  // Per step only the wave-uniform row offset changes (soffset); rows past
+  // Without a table there is one GEMV, entered before the loop: the branch
+  // that enters another one, left in the loop, kept its uniform state apart
+  // from the first one's and spilled scalar registers (up to 47, read back
+  // 22 to 27 times in two steps of 5 words a lane).  Per step only the wave-uniform row offset changes (soffset); rows past
   // the end of a matrix fall outside its resource and read zero.
   int idi = -1;
   rsrc_t rb = make_rsrc(nullptr, 0), rg = rb, rs = rb;
@@ -229,18 +232,33 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
                    static_cast<uint32_t>(min(g0 + q, glast))) * 2u;
   };
 
+  if constexpr (!TABLE) fetch_enter(0);
+
   auto issue = [&](auto stage_c) {
     constexpr int k = decltype(stage_c)::value;
     const FastStep& s = st[k];
-    if (s.valid && s.di != idi) fetch_enter(s.di);
+    if (TABLE && s.valid && s.di != idi) fetch_enter(s.di);
     const uint32_t unit = static_cast<uint32_t>(s.row0 / R);
     // Past the last step `unit` is 0 and oob all there is.  A choice between
     // the two (s.valid ? ... : kOOB) goes through a lane mask, and takes the
     // products with it: two quarter-rate vector multiplies a step (5 bf16 words
     // on 32-lane rows: 5 of 316 vector instructions a step).
     const uint32_t soff_p = unit * row_bytes | s.oob;
+    // Four words a load (dword-aligned; dwords past the section read zero),
+    // the rest one by one: left to the compiler, which keeps every word's
+    // offset in a register of its own across the loop where the lane offset
+    // never changes, a row of 12 words a lane took 12 loads (2048 x 65536 int8:
+    // 18.8 us, with four words a load 16.2).
+    constexpr int kQuads = W / 4;
 #pragma unroll
-    for (int w = 0; w < W; ++w) P[k][w] = __builtin_amdgcn_raw_buffer_load_b32(rb, voff_p + 4u * w, soff_p, 0);
+    for (int c = 0; c < kQuads; ++c) {
+      const u32x4_t v = ld128_s(rb, voff_p + 16u * c, soff_p);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) P[k][4 * c + w] = v[w];
+    }
+#pragma unroll
+    for (int w = 4 * kQuads; w < W; ++w)
+      P[k][w] = __builtin_amdgcn_raw_buffer_load_b32(rb, voff_p + 4u * w, soff_p, 0);
     const uint32_t soff_q = unit * row_scale_bytes | s.oob | no_scales;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) SC[k][q] = __builtin_amdgcn_raw_buffer_load_b16(rs, voff_q[q], soff_q, 0);
@@ -301,9 +319,8 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     ry = make_rsrc(g.y, g.y_bytes);
   };
 
-  // GEMV d's activations by the wave itself, 16 bytes a load (dword loads,
-  // which the compiler made of it without the table, took 15 us of a 27 us
-  // launch at 8 int8 words a lane); words past the row's end read zero.
+  // Table: GEMV d's activations by the wave itself, where it enters a GEMV
+  // with others than its workgroup's first; words past the row's end read zero.
   auto load_x = [&](int d) {
     const auto& g = desc_at<TABLE>(a, d);
     const rsrc_t rx = make_rsrc(g.x, g.x_bytes);
@@ -344,13 +361,15 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     const FastStep& s = st[k];
     wait_vmem_all();
     flush_store();
-    // Entering another GEMV: its activations and scales, loaded and waited
+    // Table: entering another GEMV.  Its activations and scales, loaded and waited
     // for before the next step's loads are issued, so that no wait inside
     // the step covers those loads.
-    if (s.di != xdi) {
-      enter_x(s.di);
-      load_x(s.di);
-      wait_vmem_all();
+    if constexpr (TABLE) {
+      if (s.di != xdi) {
+        enter_x(s.di);
+        load_x(s.di);
+        wait_vmem_all();
+      }
     }
     next();
     // LDS byte address of the stage buffer, in bits, so a window's dword
@@ -360,9 +379,11 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
         static_cast<uint32_t>(reinterpret_cast<size_t>((LdsU32*)stage_buf(stage_c))) * 8u;
     // Words past the end of a row (ragged tiles only) count as empty.
     if (ragged) {
+      int nw = nwl;
+      if constexpr (W > 8) asm volatile("" : "+v"(nw));  // the words' masks, held across the loop, would be spilled
 #pragma unroll
       for (int w = 0; w < W; ++w)
-        if (w >= nwl) P[k][w] = 0u;
+        if (w >= nw) P[k][w] = 0u;
     }
     const uint32_t (&Pw)[W] = P[k];
     // Cursor: the step's first sign bit, relative to the block's first dword.
@@ -483,9 +504,11 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
   build_fast_tables<BF16, CT, NT>(tab, threadIdx.x);
   issue_signs(std::integral_constant<int, 0>{});
   bool shared = true;
-  if (st[0].valid) {
+  if constexpr (!TABLE) {
+    enter_x(0);
+  } else if (st[0].valid) {
     enter_x(st[0].di);
-    if constexpr (TABLE) {
+    {
       const auto &g = desc_at<TABLE>(a, st[0].di), &f = desc_at<TABLE>(a, fdi);
       shared = g.x == f.x && g.x_bytes == f.x_bytes;
     }

@@ -337,7 +337,8 @@ __global__ void __launch_bounds__(fixed_threads(false, BF16, BK), trit5_waves(BF
     ydst = g.y;
     ybytes = g.y_bytes;
   };
-  // GEMV d's activations by the wave itself.
+  // Table: GEMV d's activations by the wave itself, where it enters one with
+  // others than its workgroup's first.
   auto load_x = [&](int d) {
     const auto& g = desc_at<TABLE>(a, d);
     const int nbl = g.upr - b0;
@@ -382,10 +383,12 @@ __global__ void __launch_bounds__(fixed_threads(false, BF16, BK), trit5_waves(BF
     uint16_t SC0[BK];
 #pragma unroll
     for (int t = 0; t < BK; ++t) SC0[t] = SC1[t];
-    if (s0.di != xdi) {
-      enter_x(s0.di);
-      load_x(s0.di);
-      wait_vmem_all();
+    if constexpr (TABLE) {
+      if (s0.di != xdi) {
+        enter_x(s0.di);
+        load_x(s0.di);
+        wait_vmem_all();
+      }
     }
     // The next step's loads, issued after the activations of a GEMV the wave
     // enters have been waited for, so that no wait inside the step covers them.
@@ -553,7 +556,8 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
       }
     }
   };
-  // GEMV d's activations by the wave itself.
+  // Table: GEMV d's activations by the wave itself, where it enters one with
+  // others than its workgroup's first.
   auto load_x = [&](int d) {
     const auto& g = desc_at<TABLE>(a, d);
     const int nul = g.upr - u0;
@@ -598,10 +602,12 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
     for (int w = 0; w < WB; ++w) cw0[w] = cw1[w];
 #pragma unroll
     for (int q = 0; q < NQ; ++q) SC0[q] = SC1[q];
-    if (s0.di != xdi) {
-      enter_x(s0.di);
-      load_x(s0.di);
-      wait_vmem_all();
+    if constexpr (TABLE) {
+      if (s0.di != xdi) {
+        enter_x(s0.di);
+        load_x(s0.di);
+        wait_vmem_all();
+      }
     }
     // The next step's loads, issued after the activations of a GEMV the wave
     // enters have been waited for, so that no wait inside the step covers them.

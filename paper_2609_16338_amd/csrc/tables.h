@@ -93,21 +93,17 @@ __device__ __forceinline__ void build_fast_tables(FastTables<BF16, CT>& t, int t
   }
   const uint32_t glo = bytes4(g[0], g[1], g[2], g[3]), ghi = bytes4(g[4], g[5], g[6], g[7]);
   const chunk16 tv = {glo, ghi, glo, ghi};
-  [&]<int... Ws>(std::integer_sequence<int, Ws...>) {  // E: 16 chunks a row, key key0 + w
-    (([&] {
-       if (Ws % kShares != share) return;
-       chunk16 v = ev;
-       row_bcast<Ws, 0xF>(v, ev);
-       q[(key0 + Ws) * 16 + (lane & 15)] = v;
-     }()),
-     ...);
-  }(std::make_integer_sequence<int, 16>{});
   constexpr int TC = CT / 2;       // chunks per T row
   constexpr int kRows = 16 / TC;   // T rows per 16 lanes
   constexpr int kBanks = (1 << (TC / 4)) - 1;  // the DPP banks of one T row
+  const auto e_row = [&](auto w) {  // E: 16 chunks a row, key key0 + w
+    constexpr int k = decltype(w)::value;
+    chunk16 v = ev;
+    row_bcast<k, 0xF>(v, ev);
+    q[(key0 + k) * 16 + (lane & 15)] = v;
+  };
   const auto t_rows = [&](auto w) {  // T: keys key0 + kRows w ..
     constexpr int k = decltype(w)::value * kRows;
-    if (decltype(w)::value % kShares != share) return;
     chunk16 v = tv;
     row_bcast<k, kBanks>(v, tv);
     if constexpr (kRows >= 2) row_bcast<k + 1, kBanks << (TC / 4)>(v, tv);
@@ -117,9 +113,16 @@ __device__ __forceinline__ void build_fast_tables(FastTables<BF16, CT>& t, int t
     }
     q[Tb::kT / 16 + (key0 + k) * TC + (lane & 15)] = v;
   };
-  [&]<int... Ws>(std::integer_sequence<int, Ws...>) {
-    (t_rows(std::integral_constant<int, Ws>{}), ...);
-  }(std::make_integer_sequence<int, TC>{});
+  // One branch per share, not one per row: the compiler places the rows of
+  // many branches at the kernel's end, and every launch starts with the
+  // instruction cache's misses between them.
+  const auto rows = [&]<int S, int... Ws>(std::integral_constant<int, S>, std::integer_sequence<int, Ws...>) {
+    ([&] { if constexpr (Ws % kShares == S) e_row(std::integral_constant<int, Ws>{}); }(), ...);
+    ([&] { if constexpr (Ws < TC && Ws % kShares == S) t_rows(std::integral_constant<int, Ws>{}); }(), ...);
+  };
+  [&]<int... Ss>(std::integer_sequence<int, Ss...>) {
+    ([&] { if (share == Ss) rows(std::integral_constant<int, Ss>{}, std::make_integer_sequence<int, 16>{}); }(), ...);
+  }(std::make_integer_sequence<int, kShares>{});
 }
 
 // int8 arithmetic of one word from deposit-form lookups: perm(T[s], E[m])

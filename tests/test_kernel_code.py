@@ -34,3 +34,13 @@ def test_streaming_step_offsets_are_scalar(seg):
     assert len(bodies) >= 2 * (16 + 8) * 2
     bad = {name: found for name, body in bodies.items() if (found := _vector_products_read_back(body))}
     assert not bad, f"{len(bad)} of {len(bodies)} kernels, e.g. {next(iter(bad.items()))}"
+
+
+def test_streaming_kernels_do_not_spill():
+    """Every instantiation keeps its state in registers (a spilled scalar register is read
+    back with a vector instruction inside the step loop)."""
+    found = {name: (k[".sgpr_spill_count"], k[".vgpr_spill_count"]) for name, k in code_objects.kernels().items()
+             if re.search(r"bitcos_(fast|diag)_kernel<", name)}
+    assert len(found) > 400
+    spilled = {name: n for name, n in found.items() if any(n)}
+    assert not spilled, f"{len(spilled)} of {len(found)} kernels: {sorted(spilled.items())[:5]}"
