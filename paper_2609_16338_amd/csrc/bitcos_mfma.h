@@ -203,7 +203,7 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
     u0 = (S0 - fbeg + fC - 1) / fC;
     if (fbeg + u0 * fC >= fend) {  // no unit of this GEMV starts in the share
       has = fend < U1;
-      if (has) fetch_enter(fdi + 1);
+      if (TABLE && has) fetch_enter(fdi + 1);
       u0 = 0;
     }
     has = has && fbeg + u0 * fC < U1;
@@ -301,7 +301,7 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
       const int start = fbeg + (s.unit + 1) * fC;
       const bool same = start < fend;
       n.valid = start < U1;
-      if (n.valid && !same) fetch_enter(fdi + 1);
+      if (TABLE && n.valid && !same) fetch_enter(fdi + 1);
       n.di = fdi;
       n.unit = same ? s.unit + 1 : 0;
       n.c = 0;
@@ -450,10 +450,11 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
   place(cur);
   stage_signs(cur);
 
+  if constexpr (!TABLE) decode_enter(0);
   for (;;) {
     const MStep cs = fs;
     if (!cs.valid) break;
-    if (cs.di != ddi) decode_enter(cs.di);
+    if (TABLE && cs.di != ddi) decode_enter(cs.di);
 
     // Fetch step t+1.  offn holds the offsets of the unit after step t's:
     // step t+1's own when it starts a unit.
@@ -566,12 +567,14 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
 
     if (whole && cs.last) {  // store the unit: y[m][row]; rows past n and batch rows past M are dropped
       const int row0 = cs.unit * kRows;
+      int n_out = __builtin_amdgcn_readfirstlane(dn);
+      asm volatile("" : "+s"(n_out));  // the rows' offsets, held across the loop, would cost four registers
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         const int row = row0 + kMfmaTile * r + nr;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const uint32_t off = row < dn ? (static_cast<uint32_t>((4 * g + i) * dn) + row) * 4u : kOOB;
+          const uint32_t off = row < n_out ? (static_cast<uint32_t>((4 * g + i) * n_out) + row) * 4u : kOOB;
           put_y(finish(acc[r][i], iacc[r][i]), ry, off, 0, dadd, raw);
           acc[r][i] = 0.0f;
           iacc[r][i] = 0;
@@ -588,6 +591,8 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
   // Split units: every part's sums go to its wave's sign stage (8 of 64
   // lanes' values, 2 KB), and each of the unit's waves adds 8 / split of
   // them over the parts, in order, and stores.
+  // The lane's number is counted anew: kept across the loop, it would be spilled.
+  const int ln = static_cast<int>(__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)));
   uint32_t* const sums = sstage;
   constexpr int kSumStride = kRows * kSignStride;
   static_assert(kSumStride >= RT * 4 * kWave, "a wave's sums fit its sign stage");
@@ -597,12 +602,12 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
   for (int r = 0; r < RT; ++r)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      sums[wv * kSumStride + (4 * r + i) * kWave + lane] =
+      sums[wv * kSumStride + (4 * r + i) * kWave + ln] =
           ints ? static_cast<uint32_t>(iacc[r][i]) : __builtin_bit_cast(uint32_t, acc[r][i]);
   __syncthreads();
   if (S0 >= U1) return;
   for (int v = part; v < RT * 4; v += split) {
-    const uint32_t* p = sums + (wv - part) * kSumStride + v * kWave + lane;
+    const uint32_t* p = sums + (wv - part) * kSumStride + v * kWave + ln;
     float f = 0.0f;
     int n = 0;
     for (int k = 0; k < split; ++k) {
@@ -612,8 +617,8 @@ __global__ void __launch_bounds__(kMfmaThreads) bitcos_mfma_kernel(const KernelA
       else
         f += __builtin_bit_cast(float, w);
     }
-    const int row = u0 * kRows + kMfmaTile * (v >> 2) + nr;
-    const uint32_t off = row < dn ? (static_cast<uint32_t>((4 * g + (v & 3)) * dn) + row) * 4u : kOOB;
+    const int row = u0 * kRows + kMfmaTile * (v >> 2) + (ln & 15);
+    const uint32_t off = row < dn ? (static_cast<uint32_t>((4 * (ln >> 4) + (v & 3)) * dn) + row) * 4u : kOOB;
     put_y(finish(f, n), ry, off, 0, dadd, raw);
   }
 }
