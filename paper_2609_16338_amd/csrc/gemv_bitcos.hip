@@ -89,7 +89,7 @@ int launch_bitcos(const BatchHeader& h, const GemvDesc* table_dev, const GemvDes
   const int threads = diag        ? bitcos_k::diag_threads(h.per_lane, bf16)
                       : streaming ? bitcos_k::fast_threads(h.per_lane, bf16)
                                   : (bf16 ? bitcos_k::Cfg<true>::kThreads : bitcos_k::Cfg<false>::kThreads);
-  const int64_t blocks = persistent_blocks(reinterpret_cast<const void*>(fn), h.total_units, threads);
+  const int64_t blocks = persistent_blocks(reinterpret_cast<const void*>(fn), h.total_units, threads, streaming);
   if (blocks <= 0 || blocks > 0x7FFFFFFF) return BITCOS_E_HIP;
   hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(threads), 0,
                      static_cast<hipStream_t>(stream), a);
@@ -114,7 +114,7 @@ static int launch_bitcos_long(const GemvDesc& d, int per_lane, bool bf16, void* 
   a.one.units = d.n;
   a.one.offset_stride = 1;
   const int threads = bitcos_k::fast_threads(per_lane, bf16);
-  int64_t blocks = persistent_blocks(reinterpret_cast<const void*>(fn), d.n, threads);
+  int64_t blocks = persistent_blocks(reinterpret_cast<const void*>(fn), d.n, threads, true);
   if (blocks <= 0) return BITCOS_E_HIP;
   const int64_t least = (static_cast<int64_t>(d.n) + bitcos_k::kLongRows - 1) / bitcos_k::kLongRows;
   if (blocks < least) blocks = least;

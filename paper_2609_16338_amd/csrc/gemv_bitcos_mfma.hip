@@ -30,7 +30,7 @@ int launch_bitcos_mfma(const BatchHeader& h, const GemvDesc* table_dev, const Ge
   constexpr int threads = bitcos_k::kMfmaThreads;
   // Split units: every part has its wave.  Whole ones: a persistent grid.
   const int64_t blocks = h.split > 1 ? (h.total_units * h.split * 64 + threads - 1) / threads
-                                     : persistent_blocks(reinterpret_cast<const void*>(fn), h.total_units, threads);
+                                     : persistent_blocks(reinterpret_cast<const void*>(fn), h.total_units, threads, false);
   if (blocks <= 0 || blocks > 0x7FFFFFFF) return BITCOS_E_HIP;
   hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(threads), 0,
                      static_cast<hipStream_t>(stream), a);

@@ -28,7 +28,7 @@ int launch_fixed(const BatchHeader& h, const GemvDesc* table_dev, const GemvDesc
   a.pad = 0;
   a.one = one;
   const int threads = fixed_k::fixed_threads(h.format == BITCOS_FMT_BIT2, bf16, h.per_lane);
-  const int64_t blocks = persistent_blocks(reinterpret_cast<const void*>(fn), h.total_units, threads);
+  const int64_t blocks = persistent_blocks(reinterpret_cast<const void*>(fn), h.total_units, threads, true);
   if (blocks <= 0 || blocks > 0x7FFFFFFF) return BITCOS_E_HIP;
   hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(threads), 0,
                      static_cast<hipStream_t>(stream), a);

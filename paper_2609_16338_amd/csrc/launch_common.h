@@ -49,17 +49,19 @@ inline int bitcos_cus() {
 }
 
 // Blocks of `threads` threads for a persistent launch over `units` work units:
-// as many as the GPU keeps resident at once, no more than a wave per unit
-// needs, but at least a block on every CU while there are units for them
-// (the kernels spread a launch's units over all of its blocks).  -1 on a HIP
-// error.
-inline int64_t persistent_blocks(const void* fn, int64_t units, int threads = 256) {
+// as many as the GPU keeps resident at once, and no more than a wave per unit
+// needs; with `spread`, at least a block on every CU while there are units for
+// them, for the kernels that deal a launch's units out over all of its blocks
+// (unit_range).  The others give the first waves a whole run of units each, so
+// more blocks would build their tables for nothing (2560 x 256 with 16 rows:
+// 8.1 us with 10 blocks, 8.2 with 80).  -1 on a HIP error.
+inline int64_t persistent_blocks(const void* fn, int64_t units, int threads, bool spread) {
   const int cus = bitcos_cus();
   if (cus < 1) return -1;
   const int64_t resident = static_cast<int64_t>(cus) * bitcos_blocks_per_cu(fn, threads);
   const int64_t wpb = threads / 64;
   int64_t need = (units + wpb - 1) / wpb;
-  if (need < cus) need = units < cus ? units : cus;
+  if (spread && need < cus) need = units < cus ? units : cus;
   int64_t b = need < resident ? need : resident;
   return b < 1 ? 1 : b;
 }
