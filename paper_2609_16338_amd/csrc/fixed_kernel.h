@@ -43,7 +43,7 @@ struct KernelArgs {
   const GemvDesc* __restrict__ table;  // batch: descriptor table in device memory
   int64_t total_units;
   int32_t count;
-  int32_t pad;
+  int32_t per;                         // units of a wave, where waves take runs of equal length (run_range)
   GemvDesc one;                        // single GEMV: its descriptor
 };
 
@@ -91,11 +91,21 @@ struct StepGen {
   }
 };
 
-// The wave's contiguous unit range of a persistent launch (empty where
-// U >= Uend), and the GEMV the workgroup's first wave starts on.
-template <int R, bool TABLE, int WPB = kBlock / kWave>
-__device__ __forceinline__ int wave_range(const KernelArgs& a, StepGen<R, TABLE>& gen) {
-  const auto range = unit_range<WPB>(a.total_units, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+// The wave's contiguous unit range of a persistent launch: its share of the
+// launch's units dealt out evenly (unit_range).  Returns the GEMV the
+// workgroup's first wave starts on.  Totals of 32 bits, which is nearly all,
+// are divided as such: a 64-bit division is some 150 instructions at the start
+// of every wave (2-bit int8, 5120 x 2048: 3.6 -> 3.3 us).
+template <int R, bool TABLE, int WPB>
+__device__ __forceinline__ int even_range(const KernelArgs& a, StepGen<R, TABLE>& gen) {
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  UnitRange<int64_t> range;
+  if (a.total_units < (int64_t(1) << 31)) {
+    const auto r = unit_range<WPB>(static_cast<int>(a.total_units), wv);
+    range = {r.first, r.begin, r.end};
+  } else {
+    range = unit_range<WPB>(a.total_units, wv);
+  }
   gen.U = range.begin;
   gen.Uend = range.end;
   gen.di = 0;
@@ -106,6 +116,23 @@ __device__ __forceinline__ int wave_range(const KernelArgs& a, StepGen<R, TABLE>
     return f.v;
   }
   return 0;
+}
+
+// ... or a.per units of it, the first waves first (empty for the last ones).
+template <int R, bool TABLE, int WPB>
+__device__ __forceinline__ void run_range(const KernelArgs& a, StepGen<R, TABLE>& gen) {
+  const int wave = __builtin_amdgcn_readfirstlane(blockIdx.x * WPB + (threadIdx.x >> 6));
+  gen.U = static_cast<int64_t>(a.per) * wave;
+  gen.Uend = min(gen.U + a.per, a.total_units);
+  gen.di = 0;
+  if constexpr (TABLE) {  // the last descriptor that begins at or before U
+    int lo = 0, hi = a.count;
+    while (hi - lo > 1) {
+      const int mid = (lo + hi) >> 1;
+      if (((CDesc*)a.table)[mid].unit_begin <= gen.U) lo = mid; else hi = mid;
+    }
+    gen.di = __builtin_amdgcn_readfirstlane(lo);
+  }
 }
 
 // Whether GEMVs d and f have the same activations.
@@ -298,7 +325,7 @@ __global__ void __launch_bounds__(fixed_threads(false, BF16, BK), trit5_waves(BF
   using Acc = typename std::conditional<BF16, float, int>::type;
 
   StepGen<R, TABLE> gen;
-  const int fdi = wave_range<R, TABLE, WPB>(a, gen);
+  const int fdi = even_range<R, TABLE, WPB>(a, gen);
   const int lane = threadIdx.x & 63;
   const int rho = lane / SEG;
   const int j = lane % SEG;
@@ -476,12 +503,26 @@ __device__ __forceinline__ void build_bit2_bf16(Bit2TablesBf16& tb, int tid, int
   }
 }
 
+// Whether a workgroup's waves share their first activations through LDS (and
+// the launch's units are dealt out evenly): always with bf16, which builds
+// tables behind the same barriers; with int8, which has none, only where a
+// lane's activations are many.  A tile of few words starts faster when each
+// wave loads its own, in eight workgroups per CU that do not wait for each
+// other, and with runs of ceil(units / waves) units, which leave whole
+// workgroups without a start.  us, own -> shared, int8: single calls, 1 word a
+// lane (25600 x 512) 4.1 -> 5.0, 3 words (4096 x 1536) 2.9 -> 3.0, 4 words
+// (5120 x 4096) 5.0 -> 4.1, 8 words (4096 x 8192) 7.4 -> 5.1; two GEMVs of
+// 5120 rows in a table, 5 words (K = 5120) 5.6 -> 7.5, 8 words (K = 8192)
+// 9.5 -> 8.2.
+constexpr bool bit2_shares_x(bool bf16, int words, bool table) { return bf16 || words >= (table ? 6 : 4); }
+
 template <int WB, int SEG, bool BF16, bool TABLE>
 __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kernel(const KernelArgs a) {
   constexpr int NT = fixed_threads(true, BF16, WB);
   constexpr int WPB = NT / kWave;
   __shared__ typename std::conditional<BF16, Bit2TablesBf16, char>::type tab;
-  __shared__ piece_t xbuf[kXRoom];
+  constexpr bool SHARE = bit2_shares_x(BF16, WB, TABLE);
+  __shared__ piece_t xbuf[SHARE ? kXRoom : 1];
 
   constexpr int R = kWave / SEG;
   constexpr int NX = BF16 ? 8 : 4;  // activation dwords per 16-weight word
@@ -490,7 +531,13 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
   constexpr int NQ = Ends::kNQ;
 
   StepGen<R, TABLE> gen;
-  const int fdi = wave_range<R, TABLE, WPB>(a, gen);
+  int fdi = 0;
+  if constexpr (SHARE) {
+    fdi = even_range<R, TABLE, WPB>(a, gen);
+  } else {
+    run_range<R, TABLE, WPB>(a, gen);
+    if (gen.U >= gen.Uend) return;
+  }
   const int lane = threadIdx.x & 63;
   const int rho = lane / SEG;
   const int j = lane % SEG;
@@ -573,7 +620,6 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
         for (int i = 0; i < 4; ++i) xr[w][d4 + i] = q[i];
       }
     }
-    arrange_x();
   };
 
   // As in the five-trit kernel.
@@ -581,15 +627,21 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
   uint32_t cw1[WB];
   uint16_t SC1[NQ];
   load_c(s1, cw1, SC1);
-  FirstX<WB * NX / 4, SEG, NT, kXRoom> fx;
-  {
-    const auto& f = desc_at<TABLE>(a, fdi);
-    fx.fetch(make_rsrc(f.x, f.x_bytes), threadIdx.x);
+  if constexpr (SHARE) {
+    FirstX<WB * NX / 4, SEG, NT, kXRoom> fx;
+    {
+      const auto& f = desc_at<TABLE>(a, fdi);
+      fx.fetch(make_rsrc(f.x, f.x_bytes), threadIdx.x);
+    }
+    const bool shared = !s1.valid || same_x<TABLE>(a, s1.di, fdi);
+    if (s1.valid && shared) enter_x(s1.di);
+    fx.share(xbuf, threadIdx.x, j, shared && s1.valid, xr);
+    arrange_x();
+  } else if constexpr (!TABLE) {
+    enter_x(0);
+    load_x(0);
+    arrange_x();
   }
-  const bool shared = !s1.valid || same_x<TABLE>(a, s1.di, fdi);
-  if (s1.valid && shared) enter_x(s1.di);
-  fx.share(xbuf, threadIdx.x, j, shared && s1.valid, xr);
-  arrange_x();
   if constexpr (BF16) {
     build_bit2_bf16(tab, threadIdx.x, NT);
     __syncthreads();
@@ -606,6 +658,7 @@ __global__ void __launch_bounds__(fixed_threads(true, BF16, WB)) bit2_gemv_kerne
       if (s0.di != xdi) {
         enter_x(s0.di);
         load_x(s0.di);
+        arrange_x();
         wait_vmem_all();
       }
     }

@@ -25,11 +25,16 @@ int launch_fixed(const BatchHeader& h, const GemvDesc* table_dev, const GemvDesc
   a.table = table_dev;
   a.total_units = h.total_units;
   a.count = h.count;
-  a.pad = 0;
   a.one = one;
-  const int threads = fixed_k::fixed_threads(h.format == BITCOS_FMT_BIT2, bf16, h.per_lane);
-  const int64_t blocks = persistent_blocks(reinterpret_cast<const void*>(fn), h.total_units, threads, true);
+  const bool bit2 = h.format == BITCOS_FMT_BIT2;
+  const int threads = fixed_k::fixed_threads(bit2, bf16, h.per_lane);
+  const bool even = !bit2 || fixed_k::bit2_shares_x(bf16, h.per_lane, table);
+  const int64_t blocks = persistent_blocks(reinterpret_cast<const void*>(fn), h.total_units, threads, even);
   if (blocks <= 0 || blocks > 0x7FFFFFFF) return BITCOS_E_HIP;
+  const int64_t waves = blocks * (threads / 64);
+  const int64_t per = (h.total_units + waves - 1) / waves;
+  if (per > 0x7FFFFFFF) return BITCOS_E_UNSUPPORTED;  // more than 2^31 units a wave: beyond any memory
+  a.per = static_cast<int32_t>(per);
   hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(blocks)), dim3(threads), 0,
                      static_cast<hipStream_t>(stream), a);
   return bitcos_launch_status();

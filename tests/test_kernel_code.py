@@ -45,3 +45,14 @@ def test_bitcos_kernels_do_not_spill():
     assert len(found) > 500
     spilled = {name: n for name, n in found.items() if any(n)}
     assert not spilled, f"{len(spilled)} of {len(found)} kernels: {sorted(spilled.items())[:5]}"
+
+
+def test_light_2bit_int8_kernels_start_without_lds():
+    """2-bit kernels with int8 activations of a few words a lane hold nothing in LDS and
+    wait at no barrier: each wave starts by itself."""
+    ks = code_objects.kernels()
+    light = {n: k for n, k in ks.items() if (m := re.search(r"bit2_gemv_kernel<(\d+), \d+, false, (true|false)>", n))
+             and int(m.group(1)) < (6 if m.group(2) == "true" else 4)}
+    assert len(light) == 5 * (5 + 3)
+    held = {n: k[".group_segment_fixed_size"] for n, k in light.items() if k[".group_segment_fixed_size"]}
+    assert not held, f"{len(held)} of {len(light)}: {sorted(held.items())[:3]}"
