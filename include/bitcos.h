@@ -173,7 +173,11 @@ int bitcos_unpack(const bitcos_layout* L, const void* blob, size_t blob_bytes, i
  *             or added onto (BITCOS_Y_F32_ADD, BITCOS_Y_I32_RAW_ADD).
  * int8 x accumulates exactly in int32 per group and applies the scale once per
  * group in fp32; with one scale per tensor and no xscale the full int32 row
- * sum is multiplied once.  bf16 x accumulates in fp32.
+ * sum is multiplied once.  bf16 x accumulates in fp32.  The order of the fp32
+ * additions is fixed for a launch, and so are its bits on a repeat; it
+ * depends on how the launch divides its rows, so a GEMV in a batch may differ
+ * in the last bits from the same GEMV alone or in another batch.
+ * Alignment: x_dev that of its element, xscale_dev and y_dev 4 bytes.
  * Errors: E_ARG (also m outside 1..BITCOS_MAX_M), E_UNSUPPORTED (dtype or
  * shape without a kernel), E_HIP.  Paper: Sec. II-C (ternary weights
  * w = p - 2n, Eq. (2), contracted against int8 activations into int32 with
@@ -321,18 +325,21 @@ int bitcos_pack_device_noalloc(const int8_t* w_dev, const uint16_t* scales_dev, 
                                void* stream);
 
 /* ---- launch description (for measurement) ---------------------------------
- * Fills the kernel configuration a GEMV on this layout would launch with,
- * for a call (or a batch of such layouts) without activation scales (rows
- * longer than a batch-1 tile: what a batch launches; a single call may take
- * the batch-1 kernel with two waves per row instead): words
- * (or blocks) per lane, lanes per row segment, rows per wave step, waves and
- * workgroups, and which kernel runs (BITCOS_KERNEL_*).  Errors as for the
- * GEMV. */
+ * Fills the kernel configuration a batch of GEMVs on layouts like this one
+ * launches with (without activation scales): words (or blocks) per lane,
+ * lanes per row segment, rows per wave step, waves and workgroups, and which
+ * kernel runs (BITCOS_KERNEL_*).  A single call launches the same, but for
+ * m = 1 and rows of one to two batch-1 tiles (bf16 16384 < k <= 32768, int8
+ * 32768 < k <= 65536): a batch of them runs the small-batch kernel, a call
+ * the streaming kernel with two waves per row.  For the small-batch kernel
+ * the work units are those of a launch of many: 32 rows, one wave each (a
+ * launch of few gives a unit to 2, 4 or 8 waves, and may take units of 16
+ * rows).  Errors as for the GEMV. */
 #define BITCOS_KERNEL_GENERAL 1     /* BITCOS, any rows per sign offset                          */
 #define BITCOS_KERNEL_STREAMING 2   /* BITCOS batch 1, group scales: v_dot2 / v_dot4 multiply    */
 #define BITCOS_KERNEL_MATRIX 3      /* BITCOS batch 1, one scale per tensor: multiply on MFMA    */
-#define BITCOS_KERNEL_SMALL_BATCH 4 /* BITCOS, 2..16 activation rows on MFMA (and batch-1 rows   \
-                                       longer than the batch-1 tiles)                             */
+#define BITCOS_KERNEL_SMALL_BATCH 4 /* BITCOS, 2..16 activation rows on MFMA (and in batches,    \
+                                       batch-1 rows longer than the batch-1 tiles)                */
 #define BITCOS_KERNEL_FIXED 5       /* five-trit or 2-bit                                        */
 typedef struct bitcos_launch_info {
   int32_t per_lane;        /* BITCOS: 32-weight words per lane; TRIT5: 128-blocks; BIT2: 16-weight words */

@@ -111,7 +111,9 @@ inline int gemv_rows(GemvEntry gemv, const bitcos_layout* L, const void* blob_de
 
 // Batch-1 layouts with rows longer than any batch-1 tile (the activations
 // of a lane live in VGPRs: bf16 K > 16384, int8 K > 32768) run the
-// small-batch kernel with one activation row, when it takes the layout.
+// small-batch kernel with one activation row, when it takes the layout; a
+// single call of up to twice that K runs the streaming kernel with two waves
+// per row instead (gemv_bitcos.hip).
 bool batch1_on_small_batch(const bitcos_layout* L, int32_t x_dtype);
 
 constexpr int kMfmaWgWaves = 8;  // waves of a workgroup

@@ -3,8 +3,8 @@
 // batch of M activation rows multiplies every decoded weight M times: one
 // MFMA takes a decoded weight tile against all (up to 16) rows at once.  It
 // also runs batch 1 (M = 1) for rows longer than the batch-1 kernels' tiles,
-// whose activations must fit a lane's registers; here they are read per
-// step, so K has no limit.
+// whose activations must fit a lane's registers (in tables; a single call only
+// past twice a tile); here they are read per step, so K has no limit.
 //
 // Work unit: 32 output rows (two 16-row MFMA tiles) over the whole of K; a
 // wave walks its units in steps of four 128-weight scale groups.  A launch

@@ -51,6 +51,24 @@ def run(fmt, w, sc, group, x, kind, xscale=None, y_mode=N.Y_F32, unit=0):
     return y.cpu().numpy(), L
 
 
+def run_table(fmt, w, sc, group, x, kind, xscale=None, y_mode=N.Y_F32):
+    """As `run`, through a batch table of one GEMV; also the names of the kernels it launches."""
+    import torch
+    from launches import captured
+    L, blob = api.plan_and_pack(fmt, w, sc, group)
+    say(FMT_NAME[fmt], w.shape, f"group={group}", kind, "xscale" if xscale is not None else "",
+        "raw" if y_mode == N.Y_I32_RAW else "f32", "table of one")
+    m = x.shape[0]
+    y = torch.full((m, w.shape[0]), -7, dtype=torch.int32 if y_mode == N.Y_I32_RAW else torch.float32, device="cuda")
+    xs = None if xscale is None else [torch.from_numpy(np.ascontiguousarray(xscale, np.float32)).cuda()]
+    b = api.Batch([L], [torch.from_numpy(blob).cuda()], [to_dev_x(x, kind)], [y], xs, y_mode)
+    names = [name for name, _, _ in captured(b.run)]
+    y.fill_(-7)
+    b.run()
+    torch.cuda.synchronize()
+    return y.cpu().numpy(), L, names
+
+
 def group_bound(w, sc, group, x, xscale=None):
     """sum_g |S a A| per output (int8 x)."""
     n, k = w.shape

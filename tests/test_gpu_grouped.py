@@ -19,7 +19,8 @@ import pytest
 
 import oracle as O
 import workloads as wl
-from parity_checks import bf16_bound, check_bf16, check_grouped, group_bound, inputs, run, say, to_dev_x
+from parity_checks import (bf16_bound, check_bf16, check_grouped, group_bound, inputs, run, run_table, say,
+                           to_dev_x)
 
 pytestmark = pytest.mark.gpu
 
@@ -181,31 +182,34 @@ def test_repeated_runs_identical(k, group):
 
 
 # Batch-1 rows longer than every batch-1 tile: bf16 K > 16384 (a lane's
-# activations no longer fit its registers), int8 K > 32768.  They run the
-# small-batch kernel with one activation row.
+# activations no longer fit its registers), int8 K > 32768.  In a table they
+# run the small-batch kernel with one activation row (single calls of up to
+# twice that K: test_gpu_long_rows.py).
 @pytest.mark.parametrize("k,kind,group", [(16512, "bf16", 128), (25600, "bf16", 0), (25600, "bf16", 128),
                                           (32896, "int8", 0), (32896, "int8", 128)])
 def test_batch1_long_rows(k, kind, group):
     n = 37
     w, sc = inputs(n, k, 0.45, group, 30, lo=0.005, hi=0.05)
+
+    def small_batch(x, xscale=None, y_mode=N.Y_F32):
+        y, L, names = run_table(N.FMT_BITCOS, w, sc, group, x, kind, xscale, y_mode)
+        assert _kernel(L, kind) == N.KERNEL_SMALL_BATCH
+        assert len(names) == 1 and "bitcos_mfma_kernel" in names[0]
+        return y
+
     if kind == "bf16":
         xb = wl.act_bf16(1, k, wl.rng_for(130, k))
-        y, L = run(N.FMT_BITCOS, w, sc, group, xb, "bf16")
-        assert _kernel(L, "bf16") == N.KERNEL_SMALL_BATCH
-        check_bf16(y, O.dense_gemv(w, sc, group, xb, x_is_bf16_bits=True), bf16_bound(w, sc, group, xb))
+        check_bf16(small_batch(xb), O.dense_gemv(w, sc, group, xb, x_is_bf16_bits=True), bf16_bound(w, sc, group, xb))
         return
     x = wl.act_int8(1, k, wl.rng_for(131, k))
-    y, L = run(N.FMT_BITCOS, w, sc, group, x, "int8")
-    assert _kernel(L, "int8") == N.KERNEL_SMALL_BATCH
+    y = small_batch(x)
     if group == 0:
         assert np.array_equal(y, O.dense_gemv(w, sc, 0, x))
     else:
         check_grouped(y, O.dense_gemv(w, sc, group, x), group_bound(w, sc, group, x))
-    y, _ = run(N.FMT_BITCOS, w, sc, group, x, "int8", y_mode=N.Y_I32_RAW)
-    assert np.array_equal(y, O.dense_gemv_raw(w, x).astype(np.int32))
+    assert np.array_equal(small_batch(x, y_mode=N.Y_I32_RAW), O.dense_gemv_raw(w, x).astype(np.int32))
     q, a = O.quantize_activations(wl.act_bf16(1, k, wl.rng_for(132, k)))
-    y, _ = run(N.FMT_BITCOS, w, sc, group, q, "int8", xscale=a)
-    check_grouped(y, O.dense_gemv(w, sc, group, q, a), group_bound(w, sc, group, q, a))
+    check_grouped(small_batch(q, a), O.dense_gemv(w, sc, group, q, a), group_bound(w, sc, group, q, a))
 
 
 def test_batch1_long_rows_batch_table():

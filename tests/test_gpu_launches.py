@@ -50,3 +50,29 @@ def test_every_workgroup_has_units(kernel, n, k, unit, m, steps, dtype):
     waves = threads // 64
     per_wave = -(-steps // (blocks * waves))
     assert (blocks - 1) * waves * per_wave < steps, f"{blocks} workgroups of {waves} waves for {steps} units"
+
+
+KERNEL_NAMES = {N.KERNEL_GENERAL: "bitcos_gemv_kernel", N.KERNEL_STREAMING: "bitcos_fast_kernel",
+                N.KERNEL_MATRIX: "bitcos_diag_kernel", N.KERNEL_SMALL_BATCH: "bitcos_mfma_kernel"}
+
+
+@pytest.mark.parametrize("dtype", ["bfloat16", "int8"])
+@pytest.mark.parametrize("n,k,group,unit,m", [
+    (40, 2560, 0, 1, 1), (40, 2560, 128, 1, 1), (40, 2560, 0, 3, 1), (40, 2560, 128, 2, 1), (40, 2560, 0, 1, 4),
+    (40, 16384, 128, 1, 1), (40, 16512, 128, 1, 1), (5, 32768, 0, 1, 1), (5, 32896, 128, 1, 1),
+    (5, 65536, 128, 1, 1), (5, 65664, 0, 1, 1), (5, 65664, 128, 1, 16),
+])
+def test_described_kernel_is_launched(n, k, group, unit, m, dtype):
+    """bitcos_describe names what a table launches, and what a call launches but for rows of
+    one to two batch-1 tiles, which a call runs on the streaming kernel."""
+    say("route", n, k, group, unit, m, dtype)
+    L, blob = _packed(n, k, group, unit)
+    described = api.describe(L, m, N.X_I8 if dtype == "int8" else N.X_BF16).kernel
+    tile = 32768 if dtype == "int8" else 16384
+    x = torch.ones((m, k), dtype=getattr(torch, dtype), device="cuda")
+    y = torch.empty((m, n), dtype=torch.float32, device="cuda")
+    (table, _, _), = captured(api.Batch([L], [blob], [x], [y]).run)
+    assert KERNEL_NAMES[described] in table
+    (single, _, _), = captured(lambda: api.gemv(L, blob, x, y))
+    call = N.KERNEL_STREAMING if m == 1 and tile < k <= 2 * tile else described
+    assert KERNEL_NAMES[call] in single

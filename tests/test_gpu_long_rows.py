@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 api = pytest.importorskip("paper_2609_16338_amd.api")
+from launches import captured  # noqa: E402
 from paper_2609_16338_amd import _native as N  # noqa: E402
 
 
@@ -57,6 +58,12 @@ def test_long_rows_bf16(n, k):
         again = torch.empty_like(y)
         api.gemv(L, bd, xd, again)
         assert np.array_equal(first.view(np.uint32), again.cpu().numpy().view(np.uint32))
+        (name, _, _), = captured(lambda: api.gemv(L, bd, xd, again))
+        assert "bitcos_fast_kernel" in name
+        a = wl.rng_for(806, k).uniform(0.5, 2.0, size=(1, k // 128)).astype(np.float32)
+        api.gemv(L, bd, xd, y, torch.from_numpy(a).cuda())
+        refa = O.dense_gemv(w[rows], ss, group, x, a, x_is_bf16_bits=True)
+        check_bf16(y.cpu().numpy()[:, rows], refa, bound * float(a.max()))
 
 
 @pytest.mark.parametrize("n,k", [(1, 32896), (6, 36864), (9, 40960), (70, 33024), (5, 65536), (1100, 32896)])
@@ -83,5 +90,7 @@ def test_long_rows_int8(n, k):
     api.gemv(L, bd, to_dev_x(q, "int8"), f, ad)
     check_grouped(f.cpu().numpy()[:, rows], O.dense_gemv(w[rows], ss, 128, q, a), group_bound(w[rows], ss, 128, q, a))
     Lt, bt = api.plan_and_pack(N.FMT_BITCOS, w, sc[:1], 0)
+    (name, _, _), = captured(lambda: api.gemv(L, bd, xd, y, y_mode=N.Y_I32_RAW))
+    assert "bitcos_fast_kernel" in name
     api.gemv(Lt, torch.from_numpy(bt).cuda(), xd, f)  # one scale per tensor: bit-exact
     assert np.array_equal(f.cpu().numpy()[:, rows], np.asarray(O.dense_gemv(w[rows], sc[:1], 0, x), np.float32))

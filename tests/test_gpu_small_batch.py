@@ -16,8 +16,8 @@ import pytest
 
 import oracle as O
 import workloads as wl
-from parity_checks import (bf16_bound, check_bf16, check_grouped, group_bound, inputs, run, sampled_rows, say,
-                           to_dev_x)
+from parity_checks import (bf16_bound, check_bf16, check_grouped, group_bound, inputs, run, run_table,
+                           sampled_rows, say, to_dev_x)
 
 pytestmark = pytest.mark.gpu
 
@@ -110,13 +110,14 @@ def test_small_batch_activation_scales(m, group, k):
 def test_small_batch_bf16_activation_scales(m, group):
     """bf16 activations with per-group activation scales, y = sum_g S a A:
     the small-batch kernel's bf16 activation-scale variant (at m = 1 through
-    a row too long for the batch-1 kernels)."""
+    a table with a row too long for the batch-1 tiles)."""
     n, k = (37, 20480) if m == 1 else (70, 2560)
     w, sc = inputs(n, k, 0.42, group, 535 + m)
     xb = _acts("bf16", m, k, 5)
     a = wl.rng_for(536, m, k).uniform(0.5, 2.0, size=(m, k // 128)).astype(np.float32)
-    y, L = run(N.FMT_BITCOS, w, sc, group, xb, "bf16", xscale=a)
+    y, L, names = run_table(N.FMT_BITCOS, w, sc, group, xb, "bf16", xscale=a)
     assert api.describe(L, m, N.X_BF16).kernel == N.KERNEL_SMALL_BATCH
+    assert len(names) == 1 and "bitcos_mfma_kernel" in names[0]
     ref = O.dense_gemv(w, sc, group, xb, a, x_is_bf16_bits=True)
     check_bf16(y, ref, bf16_bound(w, sc, group, xb) * float(a.max()))
 

@@ -271,7 +271,8 @@ def test_describe_bit2_tiles():
 
 
 def test_describe_kernel_choice():
-    """Which kernel a batch-1 call on a layout runs (the launcher's rule)."""
+    """Which kernel a table of batch-1 GEMVs on a layout runs; a call too, but for rows longer
+    than a tile (test_gpu_launches.py has what is launched)."""
     def kind(group, unit_rows, k=2560, fmt=N.FMT_BITCOS, m=1, x=N.X_BF16):
         w = np.zeros((40, k), np.int8)
         if fmt == N.FMT_BITCOS:
