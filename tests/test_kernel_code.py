@@ -56,3 +56,19 @@ def test_light_2bit_int8_kernels_start_without_lds():
     assert len(light) == 5 * (5 + 3)
     held = {n: k[".group_segment_fixed_size"] for n, k in light.items() if k[".group_segment_fixed_size"]}
     assert not held, f"{len(held)} of {len(light)}: {sorted(held.items())[:3]}"
+
+
+def test_2bit_int8_steps_do_not_wait_for_the_last_store():
+    """A batch's 2-bit int8 step waits for its words where it masks them, so nothing in front of
+    the next step's loads waits for all memory accesses (the last step's store is among them)."""
+    bodies = code_objects.disassembly(r"bit2_gemv_kernel<(8|12|16), 64, false, true>")
+    assert len(bodies) == 3
+    waits = {}
+    for name, body in bodies.items():
+        at = body.index("s_setprio 1")
+        while not body[at].startswith("buffer_load"):
+            at -= 1
+        while any(line.startswith("buffer_load") for line in body[at - 16:at]):  # the step's first load
+            at -= 1
+        waits[name] = [line for line in body[at - 60:at] if line.startswith("s_waitcnt") and "vmcnt(0)" in line]
+    assert not any(waits.values()), waits
