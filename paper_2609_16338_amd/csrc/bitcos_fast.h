@@ -241,8 +241,9 @@ __global__ void __launch_bounds__(fast_threads(W, BF16)) bitcos_fast_kernel(cons
     const uint32_t unit = static_cast<uint32_t>(s.row0 / R);
     // Past the last step `unit` is 0 and oob all there is.  A choice between
     // the two (s.valid ? ... : kOOB) goes through a lane mask, and takes the
-    // products with it: two quarter-rate vector multiplies a step (5 bf16 words
-    // on 32-lane rows: 5 of 316 vector instructions a step).
+    // products with it: two quarter-rate vector multiplies, selects and reads
+    // back a step (5 bf16 words on 32-lane rows: 316 vector instructions a
+    // step, so 309).
     const uint32_t soff_p = unit * row_bytes | s.oob;
     // Four words a load (dword-aligned; dwords past the section read zero),
     // the rest one by one: left to the compiler, which keeps every word's
